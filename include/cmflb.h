@@ -204,8 +204,10 @@ int cmf_gather_sites(cmf_lattice *lat, const int64_t *sites, int64_t n,
  * macro), normals, central moments, the collision of eq. cm_collision with
  * phi of eq. phi_general, f* = T(u)^-1 k*, and the streaming of eq.
  * streaming on the periodic box; plus, unless CMF_FLAG_NO_STATS, the
- * statistics row of the step (see cmf_stats).  Runs of 32 steps are
- * replayed from captured HIP graphs unless CMF_FLAG_NO_GRAPH.
+ * statistics row of the step (see cmf_stats).  Small D2Q9 boxes (up to about
+ * 130000 sites) take up to 7 steps per launch, with the results of single
+ * steps bit for bit; otherwise runs of 32 steps are replayed from captured
+ * HIP graphs unless CMF_FLAG_NO_GRAPH.
  * Asynchronous; nsteps >= 0.  Errors: CMF_EINVAL (NULL lattice,
  * nsteps < 0), CMF_EHIP (launch or graph capture failed). */
 int cmf_step(cmf_lattice *lat, int64_t nsteps);
@@ -235,12 +237,15 @@ int cmf_get_launch(cmf_lattice *lat, cmf_launch *out);
 /* Set the launch shape: block in {64, 128, 192, 256}, grid >= 1 (capped at
  * the number of tiles).  Results do not depend on it (the noise is keyed by
  * the site), only the speed and the summation order of the statistics.
- * Synchronises; drops captured graphs. */
+ * From then on every step is one launch of that shape, also for the small
+ * D2Q9 boxes that otherwise take several steps per launch, until
+ * cmf_autotune.  Synchronises; drops captured graphs. */
 int cmf_set_launch(cmf_lattice *lat, int32_t block, int32_t grid);
 
 /* Autotuner: time every candidate launch shape (block 64..256 up to the
  * row length; grid 1, 2, 4, 8, 16 and 32 x the compute-unit count, and one
- * tile per workgroup) with `steps_per_trial` real steps each (after one
+ * tile per workgroup, which is the only grid of the small D2Q9 boxes that
+ * take several steps per launch) with `steps_per_trial` real steps each (after one
  * untimed step; a step = fused kernel + statistics finalize), then restore the state, step counter and statistics ring
  * exactly as they were and keep the fastest shape.  The best shape is
  * remembered for the process under (device, q, storage, rates kind, box)

@@ -51,6 +51,9 @@ constexpr int kGraphSteps = 32;
 // (down to 1) when the ring would exceed kStatRingBytes
 constexpr int kStatBatch = 8;
 constexpr size_t kStatRingBytes = (size_t)256 << 20;
+// most steps of a fused lattice (several steps per launch) per reduction
+constexpr int kFusedSlots = 64;
+constexpr size_t kFusedRingBytes = (size_t)8 << 20;
 static_assert(kGraphSteps % kStatBatch == 0, "a captured run is whole batches");
 // noise counters are distinct for steps below 2^56 (see site_normals)
 constexpr int64_t kMaxStep = (int64_t)1 << 56;
@@ -240,9 +243,12 @@ int forked_init(ForkedRun &F) {
 
 // Enqueue a run of n <= kGraphSteps steps in the forked form on stream s,
 // in batches of K steps: step(j, stream) enqueues step j (step offset j,
-// partial-sum slot j mod 2K); fin(j0, count, stream) the statistics
-// reduction of steps j0 .. j0 + count - 1 (only when `stats`), on the second
-// stream; the step counter advances by n at the end.  Used inside a graph
+// partial-sum slot j mod 2K); fin(j0, count, bump, stream) the statistics
+// reduction of steps j0 .. j0 + count - 1 (only when `stats`), which then
+// advances the step counter by bump, on the second stream; that of the last
+// batch on s itself, which would only wait for it (one step with its
+// statistics read by a following kernel, D2Q9 96 x 61: 45.4 -> 12.9 us with kSingleLevelRows); the
+// step counter advances by n at the end.  Used inside a graph
 // capture (runs of kGraphSteps) and directly (the remainder of a cmf_step
 // call), so the statistics of direct steps overlap the next steps as well.
 template <class StepFn, class FinFn>
@@ -254,15 +260,18 @@ hipError_t enqueue_forked(hipStream_t s, ForkedRun &F, bool stats, int K, int64_
     const int j0 = b * K, j1 = j0 + K < n ? j0 + K : n;
     if (stats && b >= 2) e = hipStreamWaitEvent(s, F.ev_fin[b - 2], 0);
     for (int j = j0; j < j1 && e == hipSuccess; ++j) e = step(j, s);
-    if (stats) {
-      if (e == hipSuccess) e = hipEventRecord(F.ev_step[b], s);
+    if (e != hipSuccess) break;
+    if (stats && b < nbatch - 1) {
+      e = hipEventRecord(F.ev_step[b], s);
       if (e == hipSuccess) e = hipStreamWaitEvent(F.aux, F.ev_step[b], 0);
-      if (e == hipSuccess) e = fin(j0, j1 - j0, F.aux);
+      if (e == hipSuccess) e = fin(j0, j1 - j0, 0, F.aux);
       if (e == hipSuccess) e = hipEventRecord(F.ev_fin[b], F.aux);
+    } else if (stats) {
+      if (b >= 1) e = hipStreamWaitEvent(s, F.ev_fin[b - 1], 0);
+      if (e == hipSuccess) e = fin(j0, j1 - j0, n == 1 ? 1 : 0, s);
     }
   }
-  if (stats && e == hipSuccess) e = hipStreamWaitEvent(s, F.ev_fin[nbatch - 1], 0);
-  if (e == hipSuccess) e = launch_bump_step(step_dev, n, s);
+  if (e == hipSuccess && !(stats && n == 1)) e = launch_bump_step(step_dev, n, s);
   return e;
 }
 
@@ -270,7 +279,7 @@ template <class StepFn, class FinFn>
 int run_forked(hipStream_t s, ForkedRun &F, bool stats, int K, int64_t *step_dev, StepFn step,
                FinFn fin, int n) {
   if (n < 1 || n > kGraphSteps) return fail(CMF_EINVAL, "internal: forked run of %d steps", n);
-  if (stats) {
+  if (stats && n > K) {
     int rc = forked_init(F);
     if (rc != CMF_OK) return rc;
   }
@@ -319,6 +328,9 @@ struct cmf_lattice {
   int partials_cap = 0;    // partial rows per slot
   int partials_slots = 0;  // slots allocated (2 stat_batch needed)
   int stat_batch = 1;      // steps per forked statistics reduction
+  bool shape_set = false;  // launch shape asked for (cmf_set_launch, environment)
+  int fused = 0;           // several steps per launch: rows of a tile (0: single steps)
+  int fused_slots = 0;     // partial-sum slots of its statistics
   int cus = 256;
   double *series = nullptr;
   int cap = 0;
@@ -386,6 +398,7 @@ void fill_params(const cmf_desc &d, const double *lambda, const double *amp, con
   p.nxb = (d.nx + block - 1) / block;
   p.ntiles = p.nxb * p.ny * p.nz;
   p.noise = d.kT > 0.0 ? 1 : 0;
+  p.ncx = (d.nx + kCell - 1) / kCell;
   p.rho0 = (R)d.rho0;
   for (int v = 0; v < d.q; ++v) {
     p.amp[v] = (R)amp[v];
@@ -466,6 +479,30 @@ bool lookup_tuned(const cmf_lattice *L, int *block, int *grid) {
 
 int default_block(int nx) { return nx >= 192 ? 256 : ((nx + 63) / 64) * 64; }
 
+// Small D2Q9 boxes take several steps per launch (cmflb_step_fused.hip): the
+// rows of a tile, 0 for a box that takes single steps.  The smallest tile
+// whose workgroups all run at once, one per CU, else at two per CU: within a
+// step a CU's time is that of the sites around its tile as well, so that more
+// and smaller tiles cost less until they queue (FP32 us per step in tiles of
+// 4 / 8 / 12 / 16 rows: 100^2 2.03 / 2.22 / 2.32 / 2.52, 200^2 3.38 / 3.28 /
+// 2.64 / 2.78, 256^2 4.27 / 3.36 / 3.57 / 2.88; single steps 5.99, 6.36,
+// 6.43).  Beyond two per CU the sites computed twice outweigh the launches
+// saved (400 x 300, 475 tiles of 16: 4.94 against 8.50; 700 x 500, 1408: 13.2
+// against 11.7; 512^2, 1024: FP32 9.2 against 10.3, FP16 9.5 against 8.1, FP64
+// 20.6 against 15.2).  A launch shape that was asked for keeps single steps
+// in that shape.  Boxes of this size keep their statistics in cell order
+// whether or not they can take several steps (in-place streaming and edges
+// up to kFusedSteps cannot).
+int choose_tile_rows(const cmf_lattice *L) {
+  const cmf_desc &d = L->desc;
+  if (L->q != 9 || L->shape_set) return 0;
+  const int64_t ncx = (d.nx + kCell - 1) / kCell;
+  for (int per_cu = 1; per_cu <= 2; ++per_cu)
+    for (int ty = 4; ty <= 16; ty += 4)
+      if (ncx * ((d.ny + ty - 1) / ty) <= (int64_t)per_cu * L->cus) return ty;
+  return 0;
+}
+
 int ntiles_for(const cmf_lattice *L, int block) {
   return ((L->desc.nx + block - 1) / block) * L->desc.ny * L->desc.nz;
 }
@@ -490,24 +527,38 @@ int apply_launch(cmf_lattice *L, int block, int grid, const double *amp,
   fill_step_params(L, amp, scale, pf);
   L->block = block0;
   const int nt = pf.ntiles;
-  const int g = grid < nt ? grid : nt;
+  const int rows = choose_tile_rows(L);
+  const bool cells = rows > 0;
+  const int fused = L->in_place || L->desc.nx <= kFusedSteps || L->desc.ny <= kFusedSteps ? 0 : rows;
+  pd.cells = pf.cells = cells ? 1 : 0;
+  const int g = cells ? pf.ncx * L->desc.ny : grid < nt ? grid : nt;
   const size_t slot_bytes = sizeof(double) * kPartStride * (size_t)g;
   int K = kStatBatch;
   while (K > 1 && 2 * (size_t)K * slot_bytes > kStatRingBytes) K /= 2;
-  if (g > L->partials_cap || 2 * K > L->partials_slots) {
+  int slots = 2 * K;
+  // more for launches of several steps, within kFusedRingBytes and the
+  // second-level rows of kStatBatch steps of the largest grids
+  const int nb = (g + kLevel2Threshold - 1) / kLevel2Threshold;
+  if (fused)
+    while (slots < kFusedSlots && 2 * (size_t)slots * slot_bytes <= kFusedRingBytes &&
+           2 * slots * nb <= kStatBatch * kMaxLevel2)
+      slots *= 2;
+  if (g > L->partials_cap || slots > L->partials_slots) {
     double *parts = nullptr;
-    if (hipMalloc((void **)&parts, 2 * (size_t)K * slot_bytes) != hipSuccess)
+    if (hipMalloc((void **)&parts, (size_t)slots * slot_bytes) != hipSuccess)
       return fail(CMF_ENOMEM, "hipMalloc of the statistics partials failed");
     if (L->partials) (void)hipFree(L->partials);
     L->partials = parts;
     L->partials_cap = g;
-    L->partials_slots = 2 * K;
+    L->partials_slots = slots;
   }
+  L->fused_slots = slots;
   L->stat_batch = K;
   L->block = block;
   L->pd = pd;
   L->pf = pf;
-  L->grid = g;
+  L->fused = fused;
+  L->grid = cells || grid > nt ? nt : grid;  // cell order: one workgroup per tile
   L->nparts = g;
   drop_graphs(L);
   return CMF_OK;
@@ -585,12 +636,12 @@ struct LatticeRun {
 };
 struct LatticeFin {
   cmf_lattice *L;
-  hipError_t operator()(int j0, int count, hipStream_t s) const {
+  hipError_t operator()(int j0, int count, int bump, hipStream_t s) const {
     // j0 is a multiple of stat_batch: the batch's slots are consecutive
     return launch_finalize_batch(partials_buf(L, j0 % (2 * L->stat_batch)),
                                  (int64_t)kPartStride * L->partials_cap, count, L->nparts,
-                                 L->level2, L->series, L->cap, L->step_dev, j0, 0, L->mass0, true,
-                                 s);
+                                 L->level2, L->series, L->cap, L->step_dev, j0, bump, L->mass0,
+                                 true, s);
   }
 };
 
@@ -607,6 +658,48 @@ int run_direct(cmf_lattice *L, int n) {
                       LatticeRun{L, L->parity}, LatticeFin{L}, n);
   if (rc == CMF_OK) L->parity ^= (n & 1);
   return rc;
+}
+
+// A run of n steps of a fused lattice: launches of odd numbers of steps, at
+// most kFusedSteps, as even as possible and as few as leave the state in the
+// buffer that single steps would (each launch goes from one buffer to the
+// other, so their number must be odd when n is).  The statistics of up to
+// fused_slots steps are reduced at once, on the same stream: a reduction
+// takes about as long as one launch, far less than the event waits of a
+// second stream.
+int run_fused(cmf_lattice *L, int n) {
+  const bool stats = !(L->desc.flags & CMF_FLAG_NO_STATS);
+  const int64_t pstride = (int64_t)kPartStride * L->partials_cap;
+  const int slots = L->fused_slots, kmax = kFusedSteps < slots ? kFusedSteps : slots - 1;
+  int m = (n + kmax - 1) / kmax;
+  m += (m ^ n) & 1;
+  const int pairs = (n - m) / 2;
+  hipError_t e = hipSuccess;
+  int done = 0, reduced = 0;
+  for (int c = 0; c < m && e == hipSuccess; ++c) {
+    const int k = 1 + 2 * (pairs / m + (c < pairs % m ? 1 : 0));
+    auto reduce = [&]() {
+      if (!stats || done == reduced) return hipSuccess;
+      const hipError_t x = launch_finalize_batch(L->partials, pstride, done - reduced, L->nparts, L->level2, L->series,
+                                   L->cap, L->step_dev, reduced, 0, L->mass0, true, L->stream);
+      reduced = done;
+      return x;
+    };
+    if (done + k - reduced > slots) e = reduce();
+    if (e == hipSuccess)
+      e = launch_step_fused(L->storage, L->general, L->fused, step_params(L), L->buf[L->parity],
+                            L->buf[L->parity ^ 1], L->step_dev, done, k,
+                            stats ? L->partials + (done - reduced) * pstride : nullptr, pstride,
+                            L->stream);
+    if (e == hipSuccess) {
+      L->parity ^= 1;
+      done += k;
+      if (c == m - 1) e = reduce();
+    }
+  }
+  if (e == hipSuccess) e = launch_bump_step(L->step_dev, n, L->stream);
+  if (e != hipSuccess) return fail(CMF_EHIP, "step launch failed: %s", hipGetErrorString(e));
+  return CMF_OK;
 }
 
 void release(cmf_lattice *L) {
@@ -870,6 +963,7 @@ int create_lattice(const cmf_desc *desc, void *hip_stream, void *ext, size_t ext
     const int be = env_int("CMF_BLOCK", 0), ge = env_int("CMF_GRID", 0);
     if (be == 64 || be == 128 || be == 192 || be == 256) block = be;
     if (ge > 0) grid = ge;
+    L->shape_set = be == block || ge > 0;
     rc = apply_launch(L, block, grid, L->amp, L->scale);
     if (rc != CMF_OK) {
       release(L);
@@ -989,6 +1083,12 @@ int cmf_step(cmf_lattice *L, int64_t nsteps) {
   if (nsteps < 0) return fail(CMF_EINVAL, "nsteps < 0");
   const bool graphs = !(L->desc.flags & CMF_FLAG_NO_GRAPH);
   int64_t left = nsteps;
+  while (L->fused && left > 2) {
+    const int n = left < (1 << 20) ? (int)left : 1 << 20;
+    int rc = run_fused(L, n);
+    if (rc != CMF_OK) return rc;
+    left -= n;
+  }
   while (graphs && left >= kGraphSteps) {
     if (!L->graph[L->parity]) {
       int rc = capture_graph(L, L->parity);
@@ -1164,7 +1264,11 @@ int cmf_set_launch(cmf_lattice *L, int32_t block, int32_t grid) {
     return fail(CMF_EINVAL, "block must be 64, 128, 192 or 256, got %d", block);
   if (grid < 1) return fail(CMF_EINVAL, "grid must be >= 1, got %d", grid);
   HIP_TRY(hipStreamSynchronize(L->stream));
-  return apply_launch(L, block, grid, L->amp, L->scale);
+  const bool set0 = L->shape_set;
+  L->shape_set = true;
+  const int rc = apply_launch(L, block, grid, L->amp, L->scale);
+  if (rc != CMF_OK) L->shape_set = set0;
+  return rc;
 }
 
 int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, int32_t cap,
@@ -1201,9 +1305,13 @@ int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, in
     if (b == 64 || b - 64 < L->desc.nx) blocks.push_back(b);
   std::vector<cmf_launch> done;
   int rc = CMF_OK;
+  const bool set0 = L->shape_set;
+  L->shape_set = false;
+  const bool one_tile = choose_tile_rows(L) > 0;
   for (int b : blocks) {
     std::vector<int> grids;
-    for (int m : {1, 2, 4, 8, 16, 32}) grids.push_back(m * L->cus);
+    if (!one_tile)
+      for (int m : {1, 2, 4, 8, 16, 32}) grids.push_back(m * L->cus);
     grids.push_back(ntiles_for(L, b));
     int last = -1;
     for (int g : grids) {
@@ -1232,6 +1340,7 @@ int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, in
   (void)hipFree(saved_series);
   if (rc == CMF_OK && e != hipSuccess) rc = fail(CMF_EHIP, "autotune restore failed: %s", hipGetErrorString(e));
   if (rc != CMF_OK) {
+    L->shape_set = set0;
     (void)apply_launch(L, block0, grid0, L->amp, L->scale);
     return rc;
   }
@@ -1708,10 +1817,10 @@ struct EnsembleRun {
 };
 struct EnsembleFin {
   cmf_ensemble *E;
-  hipError_t operator()(int j, int count, hipStream_t s) const {
+  hipError_t operator()(int j, int count, int bump, hipStream_t s) const {
     if (count != 1) return hipErrorInvalidValue;  // ensembles reduce step by step
     return launch_ensemble_finalize(E->storage, E->d_reps, E->n, ens_partials_buf(E, j & 1),
-                                    E->series, E->cap, E->step_dev, j, 0, E->d_mass0, true, s);
+                                    E->series, E->cap, E->step_dev, j, bump, E->d_mass0, true, s);
   }
 };
 

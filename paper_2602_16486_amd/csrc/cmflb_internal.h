@@ -15,7 +15,21 @@ constexpr int kMaxBlock = 256;
 // kMaxLevel2 workgroups (second-level rows); 256 rows per workgroup, one per
 // thread (65536 one-tile partials: 256 workgroups, one per CU)
 constexpr int kLevel2Threshold = 256;
+// partial rows that one workgroup sums directly: four per thread take less
+// time than a second launch (a D2Q9 96 x 61 step, 366 rows, read after every
+// step: 45.4 -> 12.9 us together with the last reduction of a run on its own
+// stream)
+constexpr int kSingleLevelRows = 1024;
 constexpr int kMaxLevel2 = 256;
+// A D2Q9 statistics cell: kCell consecutive sites of a lattice row from a
+// multiple of kCell on (the last cell of a row may be shorter).  In cell
+// order the partial sums are one row per cell, cell c of lattice row y at
+// row y ncx + c, each the sum of its sites in order of x: an order that does
+// not depend on how sites are dealt to workgroups.
+constexpr int kCell = 16;
+// values a cell takes in LDS: 16-byte reads stay aligned and the cells that
+// neighbouring lanes sum start on different banks
+constexpr int kCellPitch = kCell + 4;
 
 // Parameters of one lattice as the step kernels see them (kernel argument,
 // so every field lives in scalar registers).
@@ -24,6 +38,8 @@ struct StepParams {
   int32_t nx, ny, nz, nxb;  // box and x-tiles per row
   int32_t ntiles;           // nxb * ny * nz
   int32_t noise;            // kT > 0
+  int32_t cells;            // D2Q9: statistics in cell order (one-tile launches)
+  int32_t ncx;              // statistics cells per lattice row
   R rho0;
   // phi_v = sqrt(rho) amp1 amp_v (eq. phi_general): amp_v = I~_v
   // sqrt(Lambda_v (2 - Lambda_v) b_v) (sqrt(b_v) when Lambda_v = 1) and
@@ -115,6 +131,17 @@ hipError_t launch_finalize_batch(const double *partials, int64_t pstride, int co
                                  int step_off, int bump, double mass0, bool stats,
                                  hipStream_t stream);
 hipError_t launch_bump_step(int64_t *step_ptr, int64_t by, hipStream_t stream);
+
+// Several D2Q9 steps per launch (cmflb_step_fused.hip), in tiles of kCell by
+// ty sites: `nsteps` (odd, at most kFusedSteps) steps from src to dst, the
+// step index of the first *step_ptr + step_off; partial sums of step j (cell
+// order) at partials + j pstride, none when partials is NULL.  The box must
+// have nx, ny >= kFusedSteps + 1 (the region of a tile then wraps at most
+// once) and buffers below 4 GiB.
+constexpr int kFusedSteps = 7;
+hipError_t launch_step_fused(int storage, bool general, int ty, const void *params,
+                             const void *src, void *dst, const int64_t *step_ptr, int step_off,
+                             int nsteps, double *partials, int64_t pstride, hipStream_t stream);
 hipError_t launch_init_eq(int q, int storage, const ConvParams &cp,
                           const double *rho, const double *u, void *buf,
                           hipStream_t stream);

@@ -517,7 +517,7 @@ hipError_t launch_finalize_batch(const double *partials, int64_t pstride, int co
   const double *rows = partials;
   int nrows = nparts;
   int64_t rstride = pstride;
-  if (stats && nparts > kLevel2Threshold) {
+  if (stats && nparts > kSingleLevelRows) {
     int nb = (nparts + kLevel2Threshold - 1) / kLevel2Threshold;
     if (nb > kMaxLevel2) nb = kMaxLevel2;
     const int chunk = (nparts + nb - 1) / nb;

@@ -430,6 +430,46 @@ __device__ __forceinline__ void block_store_acc(const A &acc, double *out, void 
   }
 }
 
+// LDS bytes of block_store_cells for nt threads
+template <typename T>
+__host__ __device__ constexpr int cells_lds_bytes(int nt) {
+  return kNAcc * (nt / kCell * kCellPitch) * (int)sizeof(T);
+}
+
+// FP64 sum of the kCell values of a cell (16-byte aligned in LDS, zeros for
+// the sites a row's last cell lacks): four sums of four in a row, added in
+// pairs, so that the additions of a cell are not one chain.
+template <typename T>
+__device__ __forceinline__ double cell_sum(const T *v) {
+  T x[kCell];
+#pragma unroll
+  for (int j = 0; j < kCell; ++j) x[j] = v[j];
+  double s[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    s[g] = (((double)x[4 * g] + (double)x[4 * g + 1]) + (double)x[4 * g + 2]) + (double)x[4 * g + 3];
+  return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+// Cell order (see kCell): the nt threads of a workgroup hold nt consecutive
+// sites of a row; every cell of them that starts inside the row (ncells) is
+// summed by kNAcc threads, one per column, into its own row of partials.
+// One barrier and no second level.
+template <class A>
+__device__ __forceinline__ void block_store_cells(const A &acc, double *out, int ncells, void *lds) {
+  using T = typename A::lds_type;
+  const int tid = threadIdx.x, nt = blockDim.x, pitch = nt / kCell * kCellPitch;
+  T *vals = static_cast<T *>(lds);
+#pragma unroll
+  for (int k = 0; k < kNAcc; ++k)
+    vals[k * pitch + tid / kCell * kCellPitch + tid % kCell] = acc.v[k];
+  __syncthreads();
+  for (int w = tid; w < kNAcc * ncells; w += nt) {
+    const int c = w / kNAcc, k = w - c * kNAcc;
+    out[c * kPartStride + k] = cell_sum(vals + k * pitch + c * kCellPitch);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // the fused step
 // ---------------------------------------------------------------------------
@@ -553,6 +593,23 @@ __device__ __forceinline__ TileXY tile_coords(int tile, int nxb, int ny, int bx)
   return TileXY{xb * bx + (int)threadIdx.x, row % ny, row / ny};
 }
 
+// The statistics of a workgroup's tile go to its row of the partial sums, or
+// (D2Q9 one-tile launches in cell order) to the rows of the cells it covers.
+template <bool ONE, class A, class P>
+__device__ __forceinline__ void store_tile_stats(const A &acc, const P &p, double *partials,
+                                                 void *lds) {
+  if constexpr (ONE) {
+    if (p.cells) {
+      const int xb = blockIdx.x % p.nxb, y = blockIdx.x / p.nxb;
+      const int c0 = xb * ((int)blockDim.x / kCell);
+      const int nc = p.ncx - c0 < (int)blockDim.x / kCell ? p.ncx - c0 : (int)blockDim.x / kCell;
+      block_store_cells(acc, partials + ((int64_t)y * p.ncx + c0) * kPartStride, nc, lds);
+      return;
+    }
+  }
+  block_store_acc(acc, partials + (int64_t)blockIdx.x * kPartStride, lds);
+}
+
 // ONE: the grid has one workgroup per tile (every thread processes at most
 // one site, and its statistics go to the block reduction as compute-type
 // values); otherwise workgroups stride over the tiles and accumulate in FP64.
@@ -588,7 +645,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(
     if constexpr (ONE) break;
   }
   extern __shared__ double acc_lds[];
-  block_store_acc(acc, partials + (int64_t)blockIdx.x * kPartStride, acc_lds);
+  store_tile_stats<ONE>(acc, p, partials, acc_lds);
 }
 
 // In-place (AA) streaming, buffer-addressed like load_site_buf (every z
@@ -706,7 +763,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_step_aa(
     if constexpr (ONE) break;
   }
   extern __shared__ double acc_lds[];
-  block_store_acc(acc, partials + (int64_t)blockIdx.x * kPartStride, acc_lds);
+  store_tile_stats<ONE>(acc, p, partials, acc_lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -738,7 +795,9 @@ hipError_t shape(const StepParams<R> &p, const void *src, void *dst,
   // 4096^2 FP32 0.218 -> 0.205 ms; 1-2% slower for the 3-D lattices, whose
   // kernels then keep the FP64 accumulation)
   if constexpr (L::Q == 9)
-    if (grid >= p.ntiles) return go(std::true_type{}, p.ntiles, acc_lds_bytes<R>(block));
+    if (grid >= p.ntiles)
+      return go(std::true_type{}, p.ntiles, p.cells ? cells_lds_bytes<R>(block) : acc_lds_bytes<R>(block));
+  if (p.cells) return hipErrorInvalidValue;
   return go(std::false_type{}, grid, acc_lds_bytes<double>(block));
 }
 
