@@ -24,7 +24,7 @@ constexpr int kMaxLevel2 = 256;
 // A D2Q9 statistics cell: kCell consecutive sites of a lattice row from a
 // multiple of kCell on (the last cell of a row may be shorter).  In cell
 // order the partial sums are one row per cell, cell c of lattice row y at
-// row y ncx + c, each the sum of its sites in order of x: an order that does
+// row y ncx + c, each summed in one fixed order (cell_sum): an order that does
 // not depend on how sites are dealt to workgroups.
 constexpr int kCell = 16;
 // values a cell takes in LDS: 16-byte reads stay aligned and the cells that
