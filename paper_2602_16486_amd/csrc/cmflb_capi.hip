@@ -477,7 +477,27 @@ bool lookup_tuned(const cmf_lattice *L, int *block, int *grid) {
   return true;
 }
 
-int default_block(int nx) { return nx >= 192 ? 256 : ((nx + 63) / 64) * 64; }
+// Workgroup size of an untuned lattice: the one whose tiles cover a row with
+// the fewest lanes, weighted by what a lane costs in a workgroup of that size
+// (the start of a workgroup and its statistics are shared by its lanes).  One
+// tile per workgroup, D3Q27, us per step at 64 / 128 / 192 / 256 threads: nx =
+// 300 FP32 110 / 101 / 104 / 114, FP64 207 / 218 / 222 / 262; nx = 200 FP32 160 /
+// 159 / 175 / 119, FP64 317 / 314 / 412 / 309; nx = 160 FP32 147 / 162 / 138; nx =
+// 100 FP32 58 / 48.
+int default_block(int nx, int storage) {
+  const double cost[4] = {storage == kF64 ? 1.1 : 1.35, storage == kF64 ? 1.05 : 1.1, 1.1, 1.0};
+  int best = 0;
+  double least = 0.0;
+  for (int k = 0; k < 4; ++k) {
+    const int b = 64 * (k + 1);
+    const double c = (double)((nx + b - 1) / b) * b * cost[k];
+    if (!best || c < least) {
+      best = b;
+      least = c;
+    }
+  }
+  return best;
+}
 
 // Small D2Q9 boxes take several steps per launch (cmflb_step_fused.hip): the
 // rows of a tile, 0 for a box that takes single steps.  The smallest tile
@@ -505,6 +525,22 @@ int choose_tile_rows(const cmf_lattice *L) {
 
 int ntiles_for(const cmf_lattice *L, int block) {
   return ((L->desc.nx + block - 1) / block) * L->desc.ny * L->desc.nz;
+}
+
+// Workgroups of an untuned lattice.  FP32 and FP64 3-D steps wait for memory:
+// one tile per workgroup (D3Q27 FP32 / FP64 us per step against 2 per CU:
+// 50^3 14.5 / - against 20.3, 100^3 48.3 / 131 against 77.3 / 231, 128^3 82.3 / 214
+// against 128 / 366).  16-bit steps issue in every cycle and keep 16 workgroups
+// per CU, which reduce their statistics once (256^3 418 against 444 one-tile).
+// D2Q9: 1024 threads per CU below 2^22 sites (1000 x 700 FP32 15.0 against 16.4
+// one-tile, FP64 28.7 against 30.9; 1500 x 633 18.1 against 19.7), then
+// one-tile in FP32 (4096^2 219 against 236) and 16 per CU in FP64 (490 against
+// 512 one-tile).
+int default_grid(const cmf_lattice *L, int block) {
+  if (storage_bytes(L->storage) == 2) return 16 * L->cus;
+  if (L->q == 9 && L->N < ((int64_t)1 << 22)) return 4 * L->cus * (256 / block);
+  if (L->q == 9 && L->storage == kF64) return 16 * L->cus;
+  return ntiles_for(L, block);
 }
 
 void drop_graphs(cmf_lattice *L) {
@@ -951,14 +987,12 @@ int create_lattice(const cmf_desc *desc, void *hip_stream, void *ext, size_t ext
     return fail(CMF_ENOMEM, "hipMalloc of statistics buffers failed");
   }
   // launch shape: a tuned one for this key if known, else the defaults
-  // (persistent grid of 2 x CUs for 4- and 8-byte storage, 16 x CUs for
-  // 16-bit storage, which is issue-bound and wants more waves)
   {
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, L->device) == hipSuccess && prop.multiProcessorCount > 0)
       L->cus = prop.multiProcessorCount;
-    int block = default_block(desc->nx);
-    int grid = (storage_bytes(L->storage) >= 4 ? 2 : 16) * L->cus;
+    int block = default_block(desc->nx, L->storage);
+    int grid = default_grid(L, block);
     lookup_tuned(L, &block, &grid);
     const int be = env_int("CMF_BLOCK", 0), ge = env_int("CMF_GRID", 0);
     if (be == 64 || be == 128 || be == 192 || be == 256) block = be;
