@@ -5,6 +5,7 @@
 // Method: De Rosis & Zhou, "A fluctuating lattice Boltzmann formulation based
 // on orthogonal central moments" (arXiv 2602.16486).
 #include <math.h>
+#include <stddef.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -55,6 +56,8 @@ constexpr size_t kStatRingBytes = (size_t)256 << 20;
 constexpr int kFusedSlots = 64;
 constexpr size_t kFusedRingBytes = (size_t)8 << 20;
 static_assert(kGraphSteps % kStatBatch == 0, "a captured run is whole batches");
+// largest box whose structure-factor fields are transformed as one batch
+constexpr int64_t kSkBatchSites = (int64_t)1 << 22;
 // noise counters are distinct for steps below 2^56 (see site_normals)
 constexpr int64_t kMaxStep = (int64_t)1 << 56;
 
@@ -348,6 +351,7 @@ struct cmf_lattice {
   ConvParams cp;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   ForkedRun forked;
+  char *vel_ws = nullptr;  // velocity statistics: VelState, counts, block sums
   // structure factor
   int sk_nbins = 0;
   int64_t sk_M = 0, sk_samples = 0;
@@ -356,6 +360,7 @@ struct cmf_lattice {
   double *sk_acc = nullptr, *sk_out = nullptr;
   int32_t *sk_perm = nullptr;
   int64_t *sk_off = nullptr;
+  int sk_batch = 4;  // fields per transform call
   hipfftHandle sk_plan = 0;
   bool sk_has_plan = false;
 };
@@ -751,7 +756,7 @@ void release(cmf_lattice *L) {
   if (L->step_dev) (void)hipFree(L->step_dev);
   if (L->sk_has_plan) (void)hipfftDestroy(L->sk_plan);
   for (void *p : {(void *)L->sk_fields, L->sk_F, (void *)L->sk_acc, (void *)L->sk_out,
-                  (void *)L->sk_perm, (void *)L->sk_off})
+                  (void *)L->sk_perm, (void *)L->sk_off, (void *)L->vel_ws})
     if (p) (void)hipFree(p);
   forked_release(L->forked);
   if (L->own_stream && L->stream) (void)hipStreamDestroy(L->stream);
@@ -1205,8 +1210,22 @@ int cmf_sk_reset(cmf_lattice *L, int32_t nbins) {
       drop();
       return fail(CMF_ENOMEM, "structure-factor allocation failed");
     }
-    hipfftResult fr = nz > 1 ? hipfftPlan3d(&L->sk_plan, nz, ny, nx, HIPFFT_R2C)
-                             : hipfftPlan2d(&L->sk_plan, ny, nx, HIPFFT_R2C);
+    // the four fields as one batch, a quarter of the launches; one field per
+    // call for boxes that fill the chip by themselves (and whose transforms'
+    // workspace would be four times as large), or where the batch is refused
+    int dims3[3] = {nz, ny, nx};
+    const int rank = nz > 1 ? 3 : 2;
+    L->sk_batch = L->N <= kSkBatchSites ? 4 : 1;
+    hipfftResult fr = HIPFFT_SUCCESS;
+    if (L->sk_batch == 4)
+      fr = hipfftPlanMany(&L->sk_plan, rank, dims3 + 3 - rank, nullptr, 1, (int)L->N, nullptr, 1,
+                          (int)M, HIPFFT_R2C, 4);
+    if (L->sk_batch == 1 || fr != HIPFFT_SUCCESS) {
+      (void)hipGetLastError();
+      L->sk_batch = 1;
+      fr = nz > 1 ? hipfftPlan3d(&L->sk_plan, nz, ny, nx, HIPFFT_R2C)
+                  : hipfftPlan2d(&L->sk_plan, ny, nx, HIPFFT_R2C);
+    }
     if (fr != HIPFFT_SUCCESS) {
       drop();
       return fail(CMF_EHIP, "hipfft plan failed (%d)", (int)fr);
@@ -1238,7 +1257,7 @@ int cmf_sk_reset(cmf_lattice *L, int32_t nbins) {
     L->sk_off = nullptr;
     L->sk_out = nullptr;
     if (hipMalloc((void **)&L->sk_off, sizeof(int64_t) * (nbins + 1)) != hipSuccess ||
-        hipMalloc((void **)&L->sk_out, sizeof(double) * 6 * nbins) != hipSuccess)
+        hipMalloc((void **)&L->sk_out, sizeof(double) * 6 * nbins * (1 + kSkParts)) != hipSuccess)
       return fail(CMF_ENOMEM, "structure-factor allocation failed");
     HIP_TRY(hipMemcpy(L->sk_perm, perm.data(), sizeof(int32_t) * off[nbins], hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(L->sk_off, off.data(), sizeof(int64_t) * (nbins + 1), hipMemcpyHostToDevice));
@@ -1254,7 +1273,7 @@ int cmf_sk_accumulate(cmf_lattice *L) {
   if (!L) return fail(CMF_EINVAL, "lattice is NULL");
   if (!L->sk_nbins) return fail(CMF_EINVAL, "call cmf_sk_reset first");
   HIP_TRY(launch_macro_dev(L->q, L->storage, conv(L), L->buf[L->parity], L->sk_fields, L->stream));
-  for (int f = 0; f < 4; ++f) {
+  for (int f = 0; f < 4; f += L->sk_batch) {
     hipfftResult fr = hipfftExecR2C(L->sk_plan, (hipfftReal *)(L->sk_fields + f * L->N),
                                     (hipfftComplex *)L->sk_F + f * L->sk_M);
     if (fr != HIPFFT_SUCCESS) return fail(CMF_EHIP, "hipfftExecR2C failed (%d)", (int)fr);
@@ -1269,7 +1288,7 @@ int cmf_sk_shells(cmf_lattice *L, double *out, int64_t *nsamples) {
   if (!L->sk_nbins) return fail(CMF_EINVAL, "call cmf_sk_reset first");
   const int nb = L->sk_nbins;
   HIP_TRY(launch_sk_segments(L->sk_acc, L->sk_M, L->desc.nx, L->desc.ny, L->desc.nz, nb,
-                             L->sk_perm, L->sk_off, L->sk_out, L->stream));
+                             L->sk_perm, L->sk_off, L->sk_out + 6 * nb, L->sk_out, L->stream));
   HIP_TRY(hipStreamSynchronize(L->stream));
   std::vector<double> raw(6 * nb);
   HIP_TRY(hipMemcpy(raw.data(), L->sk_out, sizeof(double) * 6 * nb, hipMemcpyDeviceToHost));
@@ -1489,69 +1508,29 @@ int cmf_velocity_pdf(cmf_lattice *L, int32_t nbins, double xmax, double *moments
     return fail(CMF_EINVAL, "nbins = %d outside [1, %d]", nbins, kVelMaxBins);
   if (counts && !(xmax > 0.0 && isfinite(xmax))) return fail(CMF_EINVAL, "xmax must be > 0");
   if (!moments && !counts) return CMF_OK;
-  HIP_TRY(hipStreamSynchronize(L->stream));
-  const int grid = (int)std::min<int64_t>((L->N + 255) / 256, 1024);
-  const int nb2 = nbins + 2;
-  double *partials = nullptr, *sums = nullptr;
-  unsigned long long *dcounts = nullptr;
-  if (hipMalloc((void **)&partials, sizeof(double) * kVelCols * grid) != hipSuccess ||
-      hipMalloc((void **)&sums, sizeof(double) * kVelCols) != hipSuccess ||
-      (counts && hipMalloc((void **)&dcounts, sizeof(unsigned long long) * 3 * nb2) != hipSuccess)) {
-    if (partials) (void)hipFree(partials);
-    if (sums) (void)hipFree(sums);
+  // the workspace stays with the lattice (about 300 KB): the result, the
+  // counts right after it, the block sums
+  const size_t ncounts = counts ? 3 * ((size_t)nbins + 2) : 0;
+  const size_t result = sizeof(VelState) + sizeof(int64_t) * 3 * (kVelMaxBins + 2);
+  if (!L->vel_ws &&
+      hipMalloc((void **)&L->vel_ws, result + sizeof(double) * kVelCols * kVelGrid) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc failed");
-  }
-  const double n = (double)L->N;
-  double h[kVelCols];
-  // pass 1: the means; pass 2: central moments about them; pass 3: histogram
-  VelNorm c = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-  double mean[3], var[3], m3[3], m4[3];
-  hipError_t e = launch_vel_moments(L->q, L->storage, conv(L), L->buf[L->parity], c, grid,
-                                    partials, sums, L->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  if (e == hipSuccess) {
-    for (int a = 0; a < 3; ++a) c.centre[a] = mean[a] = h[4 * a] / n;
-    e = launch_vel_moments(L->q, L->storage, conv(L), L->buf[L->parity], c, grid, partials, sums,
-                           L->stream);
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  if (e == hipSuccess) {
-    for (int a = 0; a < 3; ++a) {
-      // central moments about the FP64 mean; the residual first moment
-      // d = sum (u - mean) / N corrects them to the exact mean
-      const double d = h[4 * a] / n, s2 = h[4 * a + 1] / n, s3 = h[4 * a + 2] / n,
-                   s4 = h[4 * a + 3] / n;
-      var[a] = s2 - d * d;
-      m3[a] = s3 - 3.0 * d * s2 + 2.0 * d * d * d;
-      m4[a] = s4 - 4.0 * d * s3 + 6.0 * d * d * s2 - 3.0 * d * d * d * d;
-      mean[a] += d;
-      c.centre[a] = mean[a];
-      c.inv_sigma[a] = var[a] > 0.0 ? 1.0 / sqrt(var[a]) : 0.0;
-    }
-    if (moments)
-      for (int a = 0; a < 3; ++a) {
-        moments[4 * a] = mean[a];
-        moments[4 * a + 1] = var[a];
-        moments[4 * a + 2] = var[a] > 0.0 ? m3[a] / (var[a] * sqrt(var[a])) : 0.0;
-        moments[4 * a + 3] = var[a] > 0.0 ? m4[a] / (var[a] * var[a]) : 0.0;
-      }
-  }
-  if (e == hipSuccess && counts) {
-    e = launch_zero_i64(reinterpret_cast<int64_t *>(dcounts), 3 * nb2, L->stream);
-    if (e == hipSuccess)
-      e = launch_vel_hist(L->q, L->storage, conv(L), L->buf[L->parity], c, grid, nbins, xmax,
-                          dcounts, L->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(counts, dcounts, sizeof(unsigned long long) * 3 * nb2,
-                         hipMemcpyDeviceToHost, L->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  }
-  (void)hipFree(partials);
-  (void)hipFree(sums);
-  if (dcounts) (void)hipFree(dcounts);
-  if (e != hipSuccess) return fail(CMF_EHIP, "velocity_pdf failed: %s", hipGetErrorString(e));
+  VelState *st = reinterpret_cast<VelState *>(L->vel_ws);
+  unsigned long long *dcounts = reinterpret_cast<unsigned long long *>(L->vel_ws + sizeof(VelState));
+  double *partials = reinterpret_cast<double *>(L->vel_ws + result);
+  // a lattice of two buffers of its own has room for the velocities in the
+  // one that the next step overwrites
+  const size_t need = sizeof(double) * (L->q == 9 ? 2 : 3) * (size_t)L->N;
+  const bool room = L->own_bufs && !L->in_place && buffer_bytes(&L->desc) >= need;
+  HIP_TRY(launch_vel_stats(L->q, L->storage, conv(L), L->buf[L->parity],
+                           room ? static_cast<double *>(L->buf[L->parity ^ 1]) : nullptr,
+                           counts ? nbins : 1, xmax, partials, st, counts ? dcounts : nullptr,
+                           L->stream));
+  std::vector<char> host(sizeof(VelState) + sizeof(int64_t) * ncounts);
+  HIP_TRY(hipMemcpyAsync(host.data(), L->vel_ws, host.size(), hipMemcpyDeviceToHost, L->stream));
+  HIP_TRY(hipStreamSynchronize(L->stream));
+  if (moments) memcpy(moments, host.data() + offsetof(VelState, moments), sizeof st->moments);
+  if (counts) memcpy(counts, host.data() + sizeof(VelState), sizeof(int64_t) * ncounts);
   return CMF_OK;
 }
 

@@ -169,19 +169,19 @@ hipError_t launch_set_i64(int64_t *p, int64_t v, hipStream_t stream);
 hipError_t launch_stream_copy(const void *src, void *dst, size_t n16,
                               hipStream_t stream);
 
-// velocity statistics (moments about a centre, normalised histograms)
+// velocity statistics (moments about the mean, normalised histograms)
 constexpr int kVelCols = 12;      // sum (u_a - c_a)^p, column 4 a + p - 1
 constexpr int kVelMaxBins = 4096;
-struct VelNorm {
-  double centre[3];
-  double inv_sigma[3];
+constexpr int kVelGrid = 2048, kVelHistGrid = 512;
+struct VelState {
+  double centre[3], inv_sigma[3];
+  double moments[12];  // mean, variance, skewness, kurtosis of each component
 };
-hipError_t launch_vel_moments(int q, int storage, const ConvParams &cp, const void *buf,
-                              const VelNorm &c, int grid, double *partials, double *out,
-                              hipStream_t stream);
-hipError_t launch_vel_hist(int q, int storage, const ConvParams &cp, const void *buf,
-                           const VelNorm &c, int grid, int nbins, double xmax,
-                           unsigned long long *counts, hipStream_t stream);
+// keep: room for dims N doubles, or NULL; partials: kVelGrid rows of kVelCols;
+// counts: 3 (nbins + 2), or NULL (no histogram)
+hipError_t launch_vel_stats(int q, int storage, const ConvParams &cp, const void *buf,
+                            double *keep, int nbins, double xmax, double *partials, VelState *st,
+                            unsigned long long *counts, hipStream_t stream);
 
 // structure factor
 hipError_t launch_macro_dev(int q, int storage, const ConvParams &cp,
@@ -190,8 +190,10 @@ hipError_t launch_sk_accumulate(const void *F, int64_t M, double inv_n,
                                 double *acc, hipStream_t stream);
 hipError_t launch_sk_shell_index(int nx, int ny, int nz, int nbins, int64_t M,
                                  int32_t *bin, hipStream_t stream);
+constexpr int kSkParts = 16;  // workgroups per shell
+// parts: nbins kSkParts rows of 6
 hipError_t launch_sk_segments(const double *acc, int64_t M, int nx, int ny, int nz,
-                              int nbins, const int32_t *perm, const int64_t *off,
+                              int nbins, const int32_t *perm, const int64_t *off, double *parts,
                               double *out, hipStream_t stream);
 
 // ensemble

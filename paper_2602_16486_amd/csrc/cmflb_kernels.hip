@@ -309,9 +309,10 @@ struct ShellGeom {
 
 __device__ __forceinline__ int shell_of(const ShellGeom &g, int64_t m,
                                         double *weight, double *kmag) {
-  const int kx = (int)(m % g.nxh);
-  const int64_t r = m / g.nxh;
-  const int ky0 = (int)(r % g.ny), kz0 = (int)(r / g.ny);
+  // modes are fewer than sites, below 2^31
+  const uint32_t um = (uint32_t)m, r = um / (uint32_t)g.nxh;
+  const int kx = (int)(um - r * (uint32_t)g.nxh);
+  const int kz0 = (int)(r / (uint32_t)g.ny), ky0 = (int)(r - (uint32_t)kz0 * (uint32_t)g.ny);
   const int ky = ky0 <= g.ny / 2 ? ky0 : ky0 - g.ny;
   const int kz = kz0 <= g.nz / 2 ? kz0 : kz0 - g.nz;
   const double two_pi = 6.283185307179586;
@@ -335,19 +336,23 @@ __global__ __launch_bounds__(256) void k_sk_shell_index(const ShellGeom g, int64
   bin[m] = shell_of(g, m, &w, &k);
 }
 
-// one workgroup per shell sums its modes (listed contiguously in `perm`,
-// shell b in [off[b], off[b + 1])) in a fixed order:
-// out[b] = (sum w k, sum w, sum w S_rho, sum w S_ux, sum w S_uy, sum w S_uz)
+// Shell sums in a fixed order: workgroup (b, p) sums part p of the modes of
+// shell b (listed contiguously in `perm`, shell b in [off[b], off[b + 1])),
+// out[b kSkParts + p] = (sum w k, sum w, sum w S_rho, sum w S_ux, sum w S_uy,
+// sum w S_uz); k_sk_total adds the parts.  One workgroup per shell left the
+// chip to the few that hold most modes (48 shells, whole call: D3Q27 128^3 216
+// -> 64 us, 256^3 1880 -> 178).
 constexpr int kSkCols = 6;
 __global__ __launch_bounds__(256) void k_sk_segments(const double *__restrict__ acc,
                                                      int64_t M, const ShellGeom g,
                                                      const int32_t *__restrict__ perm,
                                                      const int64_t *__restrict__ off,
                                                      double *__restrict__ out) {
-  __shared__ double sh[256][kSkCols];
   const int b = blockIdx.x;
+  const int64_t lo = off[b], n = off[b + 1] - lo;
+  const int64_t j1 = lo + n * (blockIdx.y + 1) / kSkParts;
   double s[kSkCols] = {0, 0, 0, 0, 0, 0};
-  for (int64_t j = off[b] + threadIdx.x; j < off[b + 1]; j += blockDim.x) {
+  for (int64_t j = lo + n * blockIdx.y / kSkParts + threadIdx.x; j < j1; j += blockDim.x) {
     const int64_t m = perm[j];
     double w, k;
     shell_of(g, m, &w, &k);
@@ -356,6 +361,7 @@ __global__ __launch_bounds__(256) void k_sk_segments(const double *__restrict__ 
 #pragma unroll
     for (int f = 0; f < 4; ++f) s[2 + f] += w * acc[f * M + m];
   }
+  __shared__ double sh[256][kSkCols];
 #pragma unroll
   for (int c = 0; c < kSkCols; ++c) sh[threadIdx.x][c] = s[c];
   __syncthreads();
@@ -365,103 +371,185 @@ __global__ __launch_bounds__(256) void k_sk_segments(const double *__restrict__ 
       for (int c = 0; c < kSkCols; ++c) sh[threadIdx.x][c] += sh[threadIdx.x + h][c];
     __syncthreads();
   }
-  if (threadIdx.x < kSkCols) out[(int64_t)b * kSkCols + threadIdx.x] = sh[0][threadIdx.x];
+  if (threadIdx.x < kSkCols)
+    out[((int64_t)b * kSkParts + blockIdx.y) * kSkCols + threadIdx.x] = sh[0][threadIdx.x];
+}
+
+__global__ __launch_bounds__(256) void k_sk_total(const double *__restrict__ parts, int n,
+                                                  double *__restrict__ out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const double *p = parts + (int64_t)(i / kSkCols) * kSkParts * kSkCols + i % kSkCols;
+  double s = p[0];
+  for (int j = 1; j < kSkParts; ++j) s += p[j * kSkCols];
+  out[i] = s;
 }
 
 // ---------------------------------------------------------------------------
 // velocity statistics of the pre-collision state (Test 7, Fig. 8): moments
-// about a given centre and normalised histograms, FP64 per site
+// about the mean and normalised histograms, FP64 per site
 // ---------------------------------------------------------------------------
+// Three passes, each needing the result of the one before (VelState, on the
+// device, so that the host waits once): the means, the central moments, the
+// histogram.  The first reads the populations, which bound it, and leaves the
+// velocities in `keep` when the caller has room for them (dims N doubles, a
+// quarter of the bytes of a D3Q27 FP32 state); the others read those, or the
+// populations again.  D3Q27 FP32 with 40 bins: 128^3 318 us with three passes
+// over the populations and the host between them, 128 now (45 + 11 + 29 us in
+// the passes; reading the state once takes 38); 256^3 711 us (433 + 89 + 29).
 template <class L, typename S>
-__device__ __forceinline__ void site_velocity(const ConvParams &cp,
-                                              const S *__restrict__ buf,
-                                              int64_t s, double u[3]) {
-  double drho, j[3];
-  site_moments<L, S>(cp, buf, (uint32_t)s, drho, j);
-  const double rho = cp.rho0 + drho;
-  u[0] = j[0] / rho;
-  u[1] = j[1] / rho;
-  u[2] = j[2] / rho;
+struct PopVelocity {
+  ConvParams cp;
+  const S *buf;
+  __device__ __forceinline__ void operator()(int64_t s, double *u) const {
+    double drho, j[3];
+    site_moments<L, S>(cp, buf, (uint32_t)s, drho, j);
+    const double rho = cp.rho0 + drho;
+    u[0] = j[0] / rho;
+    u[1] = j[1] / rho;
+    u[2] = j[2] / rho;
+  }
+};
+
+template <int DIMS>
+struct KeptVelocity {
+  const double *u;
+  int64_t n;
+  __device__ __forceinline__ void operator()(int64_t s, double *v) const {
+    v[2] = 0.0;
+#pragma unroll
+    for (int a = 0; a < DIMS; ++a) v[a] = u[a * n + s];
+  }
+};
+
+// fixed-order sum of COLS values per thread over the workgroup into out
+template <int COLS>
+__device__ __forceinline__ void block_sum_cols(const double *acc, double *out) {
+  __shared__ double sh[256][COLS];
+#pragma unroll
+  for (int k = 0; k < COLS; ++k) sh[threadIdx.x][k] = acc[k];
+  __syncthreads();
+  for (int h = 128; h >= 1; h >>= 1) {
+    if ((int)threadIdx.x < h)
+#pragma unroll
+      for (int k = 0; k < COLS; ++k) sh[threadIdx.x][k] += sh[threadIdx.x + h][k];
+    __syncthreads();
+  }
+  if (threadIdx.x < COLS) out[threadIdx.x] = sh[0][threadIdx.x];
 }
 
-// per-block sums of (u_a - c_a)^p, p = 1..4, a = x, y, z (column 4 a + p - 1),
-// each block over a fixed set of sites in a fixed order
-template <class L, typename S>
-__global__ __launch_bounds__(256) void k_vel_moments(const ConvParams cp,
-                                                     const S *__restrict__ buf,
-                                                     const VelNorm c,
-                                                     double *__restrict__ partials) {
-  const int64_t N = (int64_t)cp.nx * cp.ny * cp.nz;
-  double acc[kVelCols];
-#pragma unroll
-  for (int k = 0; k < kVelCols; ++k) acc[k] = 0.0;
+// per-block sums of u_a, each block over a fixed set of sites in a fixed order
+template <class SRC>
+__global__ __launch_bounds__(256) void k_vel_sums(const SRC src, int64_t N, int dims,
+                                                  double *__restrict__ keep,
+                                                  double *__restrict__ partials) {
+  double acc[3] = {0.0, 0.0, 0.0};
   for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < N; s += (int64_t)gridDim.x * 256) {
     double u[3];
-    site_velocity<L, S>(cp, buf, s, u);
+    src(s, u);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double v = u[a] - c.centre[a], v2 = v * v;
+      acc[a] += u[a];
+      if (keep && a < dims) keep[a * N + s] = u[a];
+    }
+  }
+  block_sum_cols<3>(acc, partials + (int64_t)blockIdx.x * kVelCols);
+}
+
+// per-block sums of (u_a - c_a)^p, p = 1..4, a = x, y, z (column 4 a + p - 1)
+template <class SRC>
+__global__ __launch_bounds__(256) void k_vel_moments(const SRC src, int64_t N,
+                                                     const VelState *__restrict__ st,
+                                                     double *__restrict__ partials) {
+  double acc[kVelCols], c[3];
+#pragma unroll
+  for (int k = 0; k < kVelCols; ++k) acc[k] = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) c[a] = st->centre[a];
+  for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < N; s += (int64_t)gridDim.x * 256) {
+    double u[3];
+    src(s, u);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double v = u[a] - c[a], v2 = v * v;
       acc[4 * a] += v;
       acc[4 * a + 1] += v2;
       acc[4 * a + 2] += v2 * v;
       acc[4 * a + 3] += v2 * v2;
     }
   }
-  __shared__ double sh[256][kVelCols];
-#pragma unroll
-  for (int k = 0; k < kVelCols; ++k) sh[threadIdx.x][k] = acc[k];
-  __syncthreads();
-  for (int h = 128; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h)
-#pragma unroll
-      for (int k = 0; k < kVelCols; ++k) sh[threadIdx.x][k] += sh[threadIdx.x + h][k];
-    __syncthreads();
-  }
-  if (threadIdx.x < kVelCols) partials[(int64_t)blockIdx.x * kVelCols + threadIdx.x] = sh[0][threadIdx.x];
+  block_sum_cols<kVelCols>(acc, partials + (int64_t)blockIdx.x * kVelCols);
 }
 
-// one workgroup: fixed-order sum of the block rows
-__global__ __launch_bounds__(256) void k_vel_moments_final(const double *__restrict__ partials,
-                                                           int nparts, double *__restrict__ out) {
-  __shared__ double sh[256][kVelCols];
-  double acc[kVelCols];
+// One workgroup: fixed-order sum of the COLS columns of the block rows, then
+// the means (COLS = 3; the counts are cleared for the histogram) or the
+// central moments about them.
+template <int COLS>
+__global__ __launch_bounds__(256) void k_vel_final(const double *__restrict__ partials, int nparts,
+                                                   double n, VelState *__restrict__ st,
+                                                   unsigned long long *__restrict__ counts,
+                                                   int ncounts) {
+  __shared__ double h[COLS];
+  double acc[COLS];
 #pragma unroll
-  for (int k = 0; k < kVelCols; ++k) acc[k] = 0.0;
+  for (int k = 0; k < COLS; ++k) acc[k] = 0.0;
   for (int b = threadIdx.x; b < nparts; b += 256)
 #pragma unroll
-    for (int k = 0; k < kVelCols; ++k) acc[k] += partials[(int64_t)b * kVelCols + k];
-#pragma unroll
-  for (int k = 0; k < kVelCols; ++k) sh[threadIdx.x][k] = acc[k];
+    for (int k = 0; k < COLS; ++k) acc[k] += partials[(int64_t)b * kVelCols + k];
+  block_sum_cols<COLS>(acc, h);
+  for (int k = threadIdx.x; k < ncounts; k += 256) counts[k] = 0ull;
   __syncthreads();
-  for (int h = 128; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h)
-#pragma unroll
-      for (int k = 0; k < kVelCols; ++k) sh[threadIdx.x][k] += sh[threadIdx.x + h][k];
-    __syncthreads();
+  if (threadIdx.x >= 3) return;
+  const int a = threadIdx.x;
+  if constexpr (COLS == 3) {
+    st->centre[a] = h[a] / n;
+  } else {
+    // central moments about the FP64 mean; the residual first moment
+    // d = sum (u - mean) / N corrects them to the exact mean
+    const double d = h[4 * a] / n, s2 = h[4 * a + 1] / n, s3 = h[4 * a + 2] / n,
+                 s4 = h[4 * a + 3] / n;
+    const double var = s2 - d * d;
+    const double m3 = s3 - 3.0 * d * s2 + 2.0 * d * d * d;
+    const double m4 = s4 - 4.0 * d * s3 + 6.0 * d * d * s2 - 3.0 * d * d * d * d;
+    const double mean = st->centre[a] + d;
+    st->centre[a] = mean;
+    st->inv_sigma[a] = var > 0.0 ? 1.0 / sqrt(var) : 0.0;
+    st->moments[4 * a] = mean;
+    st->moments[4 * a + 1] = var;
+    st->moments[4 * a + 2] = var > 0.0 ? m3 / (var * sqrt(var)) : 0.0;
+    st->moments[4 * a + 3] = var > 0.0 ? m4 / (var * var) : 0.0;
   }
-  if (threadIdx.x < kVelCols) out[threadIdx.x] = sh[0][threadIdx.x];
 }
 
 // histogram of x = (u_a - centre_a) / sigma_a: bin 0 counts x < -xmax (and
 // non-finite x), bins 1..nbins split [-xmax, xmax) evenly, bin nbins + 1
-// counts x >= xmax; LDS counters per block, integer totals (order-free)
-template <class L, typename S>
-__global__ __launch_bounds__(256) void k_vel_hist(const ConvParams cp,
-                                                  const S *__restrict__ buf,
-                                                  const VelNorm c, int dims, int nbins,
-                                                  double xmax,
+// counts x >= xmax; LDS counters per block, in `copies` sets that
+// neighbouring lanes use in turn (most sites of a Gaussian fall into a few
+// bins), integer totals (order-free)
+template <class SRC>
+__global__ __launch_bounds__(256) void k_vel_hist(const SRC src, int64_t N,
+                                                  const VelState *__restrict__ st, int dims,
+                                                  int nbins, double xmax, int copies,
                                                   unsigned long long *__restrict__ counts) {
   extern __shared__ uint32_t hist[];
   const int nb2 = nbins + 2;
-  for (int k = threadIdx.x; k < 3 * nb2; k += 256) hist[k] = 0u;
+  for (int k = threadIdx.x; k < copies * 3 * nb2; k += 256) hist[k] = 0u;
   __syncthreads();
-  const int64_t N = (int64_t)cp.nx * cp.ny * cp.nz;
+  uint32_t *own = hist + (threadIdx.x % copies) * 3 * nb2;
+  double c[3], inv[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    c[a] = st->centre[a];
+    inv[a] = st->inv_sigma[a];
+  }
   const double width = 2.0 * xmax / nbins;
   for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < N; s += (int64_t)gridDim.x * 256) {
     double u[3];
-    site_velocity<L, S>(cp, buf, s, u);
-    for (int a = 0; a < dims; ++a) {
-      const double x = (u[a] - c.centre[a]) * c.inv_sigma[a];
+    src(s, u);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if (a >= dims) continue;
+      const double x = (u[a] - c[a]) * inv[a];
       int b;
       if (!(x >= -xmax)) {
         b = 0;
@@ -471,12 +559,15 @@ __global__ __launch_bounds__(256) void k_vel_hist(const ConvParams cp,
         b = 1 + (int)floor((x + xmax) / width);
         b = b > nbins ? nbins : b;
       }
-      atomicAdd(&hist[a * nb2 + b], 1u);
+      atomicAdd(&own[a * nb2 + b], 1u);
     }
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < 3 * nb2; k += 256)
-    if (hist[k]) atomicAdd(&counts[k], (unsigned long long)hist[k]);
+  for (int k = threadIdx.x; k < 3 * nb2; k += 256) {
+    unsigned long long t = 0;
+    for (int j = 0; j < copies; ++j) t += hist[j * 3 * nb2 + k];
+    if (t) atomicAdd(&counts[k], t);
+  }
 }
 
 __global__ void k_bump_step(int64_t *step_ptr, int64_t by) {
@@ -734,39 +825,47 @@ hipError_t launch_sk_shell_index(int nx, int ny, int nz, int nbins, int64_t M,
 }
 
 hipError_t launch_sk_segments(const double *acc, int64_t M, int nx, int ny, int nz,
-                              int nbins, const int32_t *perm, const int64_t *off,
+                              int nbins, const int32_t *perm, const int64_t *off, double *parts,
                               double *out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_sk_segments, dim3(nbins), dim3(256), 0, stream, acc, M,
-                     shell_geom(nx, ny, nz, nbins), perm, off, out);
+  hipLaunchKernelGGL(k_sk_segments, dim3(nbins, kSkParts), dim3(256), 0, stream, acc, M,
+                     shell_geom(nx, ny, nz, nbins), perm, off, parts);
+  hipLaunchKernelGGL(k_sk_total, dim3(blocks_for(kSkCols * nbins, 256)), dim3(256), 0, stream,
+                     parts, kSkCols * nbins, out);
   return hipGetLastError();
 }
 
-hipError_t launch_vel_moments(int q, int storage, const ConvParams &cp, const void *buf,
-                              const VelNorm &c, int grid, double *partials, double *out,
-                              hipStream_t stream) {
-  hipError_t e = with_lattice_storage(q, storage, [&](auto lt, auto stt) {
-    using L = typename decltype(lt)::type;
-    using S = typename decltype(stt)::type;
-    hipLaunchKernelGGL((k_vel_moments<L, S>), dim3(grid), dim3(256), 0, stream, cp,
-                       static_cast<const S *>(buf), c, partials);
+hipError_t launch_vel_stats(int q, int storage, const ConvParams &cp, const void *buf,
+                            double *keep, int nbins, double xmax, double *partials, VelState *st,
+                            unsigned long long *counts, hipStream_t stream) {
+  const int64_t N = (int64_t)cp.nx * cp.ny * cp.nz;
+  const int dims = q == 9 ? 2 : 3, ncounts = counts ? 3 * (nbins + 2) : 0;
+  const int grid = (int)(blocks_for(N, 256) < (unsigned)kVelGrid ? blocks_for(N, 256) : kVelGrid);
+  // fewer workgroups for the histogram, each of which adds its counts to the
+  // totals; as many copies of its counters as 32 KB hold
+  const int hgrid = grid < kVelHistGrid ? grid : kVelHistGrid;
+  int copies = 1;
+  while (copies < 8 && 2 * copies * 3 * (nbins + 2) * (int)sizeof(uint32_t) <= 32768) copies *= 2;
+  const size_t lds = sizeof(uint32_t) * copies * 3 * (size_t)(nbins + 2);
+  auto rest = [&](auto src) {
+    using SRC = decltype(src);
+    hipLaunchKernelGGL((k_vel_moments<SRC>), dim3(grid), dim3(256), 0, stream, src, N, st, partials);
+    hipLaunchKernelGGL((k_vel_final<kVelCols>), dim3(1), dim3(256), 0, stream, partials, grid,
+                       (double)N, st, nullptr, 0);
+    if (counts)
+      hipLaunchKernelGGL((k_vel_hist<SRC>), dim3(hgrid), dim3(256), lds, stream, src, N, st, dims,
+                         nbins, xmax, copies, counts);
     return hipGetLastError();
-  });
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_vel_moments_final, dim3(1), dim3(256), 0, stream, partials, grid, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_vel_hist(int q, int storage, const ConvParams &cp, const void *buf,
-                           const VelNorm &c, int grid, int nbins, double xmax,
-                           unsigned long long *counts, hipStream_t stream) {
-  const size_t lds = sizeof(uint32_t) * 3 * (size_t)(nbins + 2);
-  const int dims = q == 9 ? 2 : 3;
+  };
   return with_lattice_storage(q, storage, [&](auto lt, auto stt) {
     using L = typename decltype(lt)::type;
     using S = typename decltype(stt)::type;
-    hipLaunchKernelGGL((k_vel_hist<L, S>), dim3(grid), dim3(256), lds, stream, cp,
-                       static_cast<const S *>(buf), c, dims, nbins, xmax, counts);
-    return hipGetLastError();
+    const PopVelocity<L, S> src{cp, static_cast<const S *>(buf)};
+    hipLaunchKernelGGL((k_vel_sums<PopVelocity<L, S>>), dim3(grid), dim3(256), 0, stream, src, N,
+                       dims, keep, partials);
+    hipLaunchKernelGGL((k_vel_final<3>), dim3(1), dim3(256), 0, stream, partials, grid, (double)N,
+                       st, counts, ncounts);
+    if (keep) return rest(KeptVelocity<L::D>{keep, N});
+    return rest(src);
   });
 }
 
