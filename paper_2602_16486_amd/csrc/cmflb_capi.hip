@@ -1190,7 +1190,8 @@ int cmf_profile_steps(cmf_lattice *L, int64_t nsteps, double *kernel_ms) {
 
 int cmf_sk_reset(cmf_lattice *L, int32_t nbins) {
   if (!L) return fail(CMF_EINVAL, "lattice is NULL");
-  if (nbins < 1 || nbins > 1024) return fail(CMF_EINVAL, "nbins must be in [1, 1024], got %d", nbins);
+  if (nbins < 1 || nbins > kSkMaxBins)
+    return fail(CMF_EINVAL, "nbins must be in [1, %d], got %d", kSkMaxBins, nbins);
   HIP_TRY(hipStreamSynchronize(L->stream));
   const int nx = L->desc.nx, ny = L->desc.ny, nz = L->desc.nz;
   const int64_t M = (int64_t)(nx / 2 + 1) * ny * nz;
@@ -1240,27 +1241,18 @@ int cmf_sk_reset(cmf_lattice *L, int32_t nbins) {
   }
   if (L->sk_nbins != nbins) {
     L->sk_nbins = 0;  // no shells until the new ones are in place
-    // shell of every mode on the device, counting sort by shell on the host
-    std::vector<int32_t> bin(M), perm(M);
-    std::vector<int64_t> off(nbins + 1, 0);
-    HIP_TRY(launch_sk_shell_index(nx, ny, nz, nbins, M, L->sk_perm, L->stream));
-    HIP_TRY(hipStreamSynchronize(L->stream));
-    HIP_TRY(hipMemcpy(bin.data(), L->sk_perm, sizeof(int32_t) * M, hipMemcpyDeviceToHost));
-    for (int64_t m = 0; m < M; ++m)
-      if (bin[m] >= 0) ++off[bin[m] + 1];
-    for (int b = 0; b < nbins; ++b) off[b + 1] += off[b];
-    std::vector<int64_t> pos(off.begin(), off.end() - 1);
-    for (int64_t m = 0; m < M; ++m)
-      if (bin[m] >= 0) perm[pos[bin[m]]++] = (int32_t)m;
     if (L->sk_off) (void)hipFree(L->sk_off);
     if (L->sk_out) (void)hipFree(L->sk_out);
     L->sk_off = nullptr;
     L->sk_out = nullptr;
     if (hipMalloc((void **)&L->sk_off, sizeof(int64_t) * (nbins + 1)) != hipSuccess ||
-        hipMalloc((void **)&L->sk_out, sizeof(double) * 6 * nbins * (1 + kSkParts)) != hipSuccess)
+        hipMalloc((void **)&L->sk_out, sizeof(double) * 6 * nbins * (1 + kSkParts)) != hipSuccess ||
+        hipMalloc((void **)&counts, sizeof(int32_t) * kSkChunks * nbins) != hipSuccess)
       return fail(CMF_ENOMEM, "structure-factor allocation failed");
-    HIP_TRY(hipMemcpy(L->sk_perm, perm.data(), sizeof(int32_t) * off[nbins], hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(L->sk_off, off.data(), sizeof(int64_t) * (nbins + 1), hipMemcpyHostToDevice));
+    hipError_t e = launch_sk_shells(nx, ny, nz, nbins, M, counts, L->sk_perm, L->sk_off, L->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+    (void)hipFree(counts);
+    if (e != hipSuccess) return fail(CMF_EHIP, "shell sort failed: %s", hipGetErrorString(e));
     L->sk_nbins = nbins;
   }
   HIP_TRY(hipMemsetAsync(L->sk_acc, 0, sizeof(double) * 4 * M, L->stream));
@@ -1397,6 +1389,7 @@ int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, in
     (void)apply_launch(L, block0, grid0, L->amp, L->scale);
     return rc;
   }
+    int32_t *counts = nullptr;
   size_t best = 0;
   for (size_t k = 1; k < done.size(); ++k)
     if (done[k].ms_per_step < done[best].ms_per_step) best = k;

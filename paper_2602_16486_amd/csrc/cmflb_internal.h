@@ -188,8 +188,11 @@ hipError_t launch_macro_dev(int q, int storage, const ConvParams &cp,
                             const void *buf, float *out, hipStream_t stream);
 hipError_t launch_sk_accumulate(const void *F, int64_t M, double inv_n,
                                 double *acc, hipStream_t stream);
-hipError_t launch_sk_shell_index(int nx, int ny, int nz, int nbins, int64_t M,
-                                 int32_t *bin, hipStream_t stream);
+constexpr int kSkMaxBins = 1024, kSkChunks = 1024;
+// perm: the M modes by shell, shell b at [off[b], off[b + 1]); counts: kSkChunks
+// nbins scratch; nbins <= kSkMaxBins
+hipError_t launch_sk_shells(int nx, int ny, int nz, int nbins, int64_t M, int32_t *counts,
+                            int32_t *perm, int64_t *off, hipStream_t stream);
 constexpr int kSkParts = 16;  // workgroups per shell
 // parts: nbins kSkParts rows of 6
 hipError_t launch_sk_segments(const double *acc, int64_t M, int nx, int ny, int nz,

@@ -327,13 +327,76 @@ __device__ __forceinline__ int shell_of(const ShellGeom &g, int64_t m,
   return b < g.nbins ? b : g.nbins - 1;
 }
 
-// shell index of every half-spectrum mode (-1 for k = 0)
-__global__ __launch_bounds__(256) void k_sk_shell_index(const ShellGeom g, int64_t M,
-                                                        int32_t *__restrict__ bin) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  double w, k;
-  bin[m] = shell_of(g, m, &w, &k);
+// The modes of every shell, in ascending order (k = 0 belongs to none): a
+// counting sort in chunks of `chunk` modes, one wave each.  First the counts
+// of every chunk,
+__global__ __launch_bounds__(64) void k_sk_count(const ShellGeom g, int64_t M, int64_t chunk,
+                                                 int32_t *__restrict__ counts) {
+  extern __shared__ int32_t cnt[];
+  for (int b = threadIdx.x; b < g.nbins; b += 64) cnt[b] = 0;
+  __syncthreads();
+  const int64_t lo = blockIdx.x * chunk, hi = lo + chunk < M ? lo + chunk : M;
+  for (int64_t m = lo + threadIdx.x; m < hi; m += 64) {
+    double w, k;
+    const int b = shell_of(g, m, &w, &k);
+    if (b >= 0) atomicAdd(&cnt[b], 1);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < g.nbins; b += 64) counts[(int64_t)blockIdx.x * g.nbins + b] = cnt[b];
+}
+
+// then the start of every shell (off, nbins + 1 entries) and, in place of the
+// counts, of every chunk's part of it (one workgroup of 1024 >= nbins threads),
+__global__ __launch_bounds__(1024) void k_sk_starts(int32_t *__restrict__ counts, int nchunks,
+                                                    int nbins, int64_t *__restrict__ off) {
+  __shared__ int64_t sum[1024];
+  const int b = threadIdx.x;
+  int64_t total = 0;
+  if (b < nbins)
+    for (int c = 0; c < nchunks; ++c) total += counts[(int64_t)c * nbins + b];
+  sum[b] = total;
+  __syncthreads();
+  for (int h = 1; h < 1024; h *= 2) {
+    const int64_t below = b >= h ? sum[b - h] : 0;
+    __syncthreads();
+    sum[b] += below;
+    __syncthreads();
+  }
+  if (b >= nbins) return;
+  off[b + 1] = sum[b];
+  if (b == 0) off[0] = 0;
+  int64_t at = sum[b] - total;  // modes are fewer than 2^31
+  for (int c = 0; c < nchunks; ++c) {
+    const int32_t n = counts[(int64_t)c * nbins + b];
+    counts[(int64_t)c * nbins + b] = (int32_t)at;
+    at += n;
+  }
+}
+
+// then the modes: 64 at a time, each after the lanes below it with its shell
+__global__ __launch_bounds__(64) void k_sk_scatter(const ShellGeom g, int64_t M, int64_t chunk,
+                                                   const int32_t *__restrict__ starts,
+                                                   int32_t *__restrict__ perm) {
+  extern __shared__ int32_t cnt[];
+  for (int b = threadIdx.x; b < g.nbins; b += 64) cnt[b] = starts[(int64_t)blockIdx.x * g.nbins + b];
+  __syncthreads();
+  const int64_t lo = blockIdx.x * chunk, hi = lo + chunk < M ? lo + chunk : M;
+  const int lane = threadIdx.x;
+  for (int64_t m0 = lo; m0 < hi; m0 += 64) {
+    const int64_t m = m0 + lane;
+    double w, k;
+    const int b = m < hi ? shell_of(g, m, &w, &k) : -1;
+    uint64_t left = __ballot(b >= 0);
+    while (left) {  // one shell per turn, that of the lowest lane left
+      const int shell = __shfl(b, __ffsll((unsigned long long)left) - 1);
+      const uint64_t same = __ballot(b == shell);
+      const int base = cnt[shell];
+      if (b == shell) perm[base + __popcll(same & (((uint64_t)1 << lane) - 1))] = (int32_t)m;
+      if (lane == 0) cnt[shell] = base + __popcll(same);
+      __syncthreads();
+      left &= ~same;
+    }
+  }
 }
 
 // Shell sums in a fixed order: workgroup (b, p) sums part p of the modes of
@@ -817,10 +880,16 @@ ShellGeom shell_geom(int nx, int ny, int nz, int nbins) {
   return g;
 }
 
-hipError_t launch_sk_shell_index(int nx, int ny, int nz, int nbins, int64_t M,
-                                 int32_t *bin, hipStream_t stream) {
-  hipLaunchKernelGGL(k_sk_shell_index, dim3(blocks_for(M, 256)), dim3(256), 0, stream,
-                     shell_geom(nx, ny, nz, nbins), M, bin);
+hipError_t launch_sk_shells(int nx, int ny, int nz, int nbins, int64_t M, int32_t *counts,
+                            int32_t *perm, int64_t *off, hipStream_t stream) {
+  const ShellGeom g = shell_geom(nx, ny, nz, nbins);
+  int64_t chunk = ((M + kSkChunks - 1) / kSkChunks + 63) / 64 * 64;
+  if (chunk < 512) chunk = 512;
+  const int nchunks = (int)((M + chunk - 1) / chunk);
+  const size_t lds = sizeof(int32_t) * nbins;
+  hipLaunchKernelGGL(k_sk_count, dim3(nchunks), dim3(64), lds, stream, g, M, chunk, counts);
+  hipLaunchKernelGGL(k_sk_starts, dim3(1), dim3(1024), 0, stream, counts, nchunks, nbins, off);
+  hipLaunchKernelGGL(k_sk_scatter, dim3(nchunks), dim3(64), lds, stream, g, M, chunk, counts, perm);
   return hipGetLastError();
 }
 
