@@ -51,7 +51,7 @@ constexpr int kGraphSteps = 32;
 // partial sums go to a ring of 2 K slots, K = kStatBatch, or fewer steps
 // (down to 1) when the ring would exceed kStatRingBytes
 constexpr int kStatBatch = 8;
-constexpr size_t kStatRingBytes = (size_t)256 << 20;
+constexpr size_t kStatRingBytes = (size_t)256 << 20, kEnsRingBytes = (size_t)16 << 20;
 // most steps of a fused lattice (several steps per launch) per reduction
 constexpr int kFusedSlots = 64;
 constexpr size_t kFusedRingBytes = (size_t)8 << 20;
@@ -204,7 +204,7 @@ void mode_constants(const cmf_desc *desc, ModeConstants &mc) {
 
 // Captured runs of kGraphSteps steps: step j passes step offset j and runs
 // on the caller's stream; the steps go in batches of K consecutive steps
-// (K = the lattice's stat_batch, at most kStatBatch; 1 for an ensemble),
+// (K = the lattice's or ensemble's stat_batch, at most kStatBatch),
 // step j writing its partial sums to slot j mod 2K; once a batch is done,
 // one statistics reduction for all its steps runs on a second stream
 // (default priority), overlapping the next batch; the first step of batch
@@ -1715,7 +1715,9 @@ struct cmf_ensemble {
   std::vector<Rep> reps;
   std::vector<ModeConstants> mcs;
   int spt9 = kEnsembleSpt9, spt3d = kEnsembleSpt27;  // sites per thread of a tile
-  int tiles_cap = 0;  // tiles the tile map and the partials are allocated for
+  int tiles_cap = 0;  // tiles the tile map is allocated for
+  size_t parts_cap = 0;  // partial rows allocated: 2 stat_batch per tile needed
+  int stat_batch = 1;    // steps per statistics reduction
   void *arena[2] = {nullptr, nullptr};
   size_t arena_bytes = 0;
   int parity = 0;
@@ -1804,8 +1806,8 @@ int ens_enqueue_step(cmf_ensemble *E) {
   HIP_TRY(launch_ensemble_step(E->storage, E->general, E->d_reps, E->d_tile_rep, E->ntiles,
                                E->arena[E->parity], E->arena[1 - E->parity], E->step_dev, 0,
                                ens_partials_buf(E, 0), E->stream));
-  HIP_TRY(launch_ensemble_finalize(E->storage, E->d_reps, E->n, ens_partials_buf(E, 0), E->series,
-                                   E->cap, E->step_dev, 0, 1, E->d_mass0,
+  HIP_TRY(launch_ensemble_finalize(E->storage, E->d_reps, E->n, ens_partials_buf(E, 0), 0, 1,
+                                   E->series, E->cap, E->step_dev, 0, 1, E->d_mass0,
                                    !(E->flags & CMF_FLAG_NO_STATS), E->stream));
   E->parity ^= 1;
   return CMF_OK;
@@ -1818,28 +1820,30 @@ struct EnsembleRun {
     const int b = parity ^ (j & 1);
     return launch_ensemble_step(E->storage, E->general, E->d_reps, E->d_tile_rep,
                                 E->ntiles, E->arena[b], E->arena[b ^ 1], E->step_dev, j,
-                                ens_partials_buf(E, j & 1), s);
+                                ens_partials_buf(E, j % (2 * E->stat_batch)), s);
   }
 };
 struct EnsembleFin {
   cmf_ensemble *E;
-  hipError_t operator()(int j, int count, int bump, hipStream_t s) const {
-    if (count != 1) return hipErrorInvalidValue;  // ensembles reduce step by step
-    return launch_ensemble_finalize(E->storage, E->d_reps, E->n, ens_partials_buf(E, j & 1),
-                                    E->series, E->cap, E->step_dev, j, bump, E->d_mass0, true, s);
+  hipError_t operator()(int j0, int count, int bump, hipStream_t s) const {
+    // j0 is a multiple of stat_batch: the batch's slots are consecutive
+    return launch_ensemble_finalize(E->storage, E->d_reps, E->n,
+                                    ens_partials_buf(E, j0 % (2 * E->stat_batch)),
+                                    (int64_t)kPartStride * E->ntiles, count, E->series, E->cap,
+                                    E->step_dev, j0, bump, E->d_mass0, true, s);
   }
 };
 
 int ens_capture(cmf_ensemble *E, int parity) {
   const bool stats = !(E->flags & CMF_FLAG_NO_STATS);
-  return capture_forked(E->stream, E->forked, stats, 1, E->step_dev, EnsembleRun{E, parity},
-                        EnsembleFin{E}, &E->graph[parity]);
+  return capture_forked(E->stream, E->forked, stats, E->stat_batch, E->step_dev,
+                        EnsembleRun{E, parity}, EnsembleFin{E}, &E->graph[parity]);
 }
 
 int ens_run_direct(cmf_ensemble *E, int n) {
   const bool stats = !(E->flags & CMF_FLAG_NO_STATS);
-  int rc = run_forked(E->stream, E->forked, stats, 1, E->step_dev, EnsembleRun{E, E->parity},
-                      EnsembleFin{E}, n);
+  int rc = run_forked(E->stream, E->forked, stats, E->stat_batch, E->step_dev,
+                      EnsembleRun{E, E->parity}, EnsembleFin{E}, n);
   if (rc == CMF_OK) E->parity ^= (n & 1);
   return rc;
 }
@@ -1876,7 +1880,14 @@ int ens_build_tiles(cmf_ensemble *E, int spt9, int spt3d) {
       tile_rep.insert(tile_rep.end(), ntl[r], r);
     }
   const int nt = (int)tile_rep.size();
-  if (nt > E->tiles_cap) {
+  // statistics of K steps per reduction, as a lattice, while the partial sums
+  // stay within kEnsRingBytes (64 replicas of 64 x 48: 478 -> 365 us
+  // per 32 graph-replayed steps, 754 -> 313 per 31 direct ones; the
+  // 0.95 ms steps of the 320-replica set hide one reduction per step)
+  int K = kStatBatch;
+  while (K > 1 && 2 * (size_t)K * sizeof(double) * kPartStride * nt > kEnsRingBytes) K /= 2;
+  const size_t rows = 2 * (size_t)K * nt;
+  if (nt > E->tiles_cap || rows > E->parts_cap) {
     // allocate first, so that a failure leaves the current tiling usable
     int32_t *map = nullptr;
     double *parts = nullptr;
@@ -2024,7 +2035,9 @@ int cmf_ensemble_create(const cmf_desc *descs, int32_t n, void *hip_stream, cmf_
 }
 
 int cmf_ensemble_destroy(cmf_ensemble *E) {
+    E->parts_cap = rows;
   if (!E) return fail(CMF_EINVAL, "ensemble is NULL");
+  E->stat_batch = K;
   ens_release(E);
   return CMF_OK;
 }
@@ -2222,8 +2235,8 @@ int cmf_ensemble_profile_steps(cmf_ensemble *E, int64_t nsteps, double *kernel_m
                                ens_partials_buf(E, 0), E->stream);
     if (e == hipSuccess) e = hipEventRecord(ev[2 * s + 1], E->stream);
     if (e == hipSuccess)
-      e = launch_ensemble_finalize(E->storage, E->d_reps, E->n, ens_partials_buf(E, 0), E->series,
-                                   E->cap, E->step_dev, 0, 1, E->d_mass0,
+      e = launch_ensemble_finalize(E->storage, E->d_reps, E->n, ens_partials_buf(E, 0), 0, 1,
+                                   E->series, E->cap, E->step_dev, 0, 1, E->d_mass0,
                                    !(E->flags & CMF_FLAG_NO_STATS), E->stream);
     E->parity ^= 1;
   }

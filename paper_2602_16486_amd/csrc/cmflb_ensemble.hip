@@ -138,17 +138,20 @@ __global__ __launch_bounds__(kEnsembleBlock) void k_ensemble_step(
   block_store_acc(acc, partials + (int64_t)tile * kPartStride, acc_lds);
 }
 
-// per-replica fixed-order sum of its tiles' partials into its series row
+// per-replica fixed-order sum of its tiles' partials into its series row, for
+// step y of a batch (partials + y pstride)
 template <typename R>
 __global__ __launch_bounds__(256) void k_ensemble_reduce(
     const ReplicaParams<R> *__restrict__ reps, const double *__restrict__ partials,
-    double *__restrict__ series, int cap, const int64_t *__restrict__ step_ptr,
+    int64_t pstride, double *__restrict__ series, int cap, const int64_t *__restrict__ step_ptr,
     int step_off, const double *__restrict__ mass0) {
   __shared__ double tot[kNAcc];
   const int r = blockIdx.x;
+  // a ring shorter than the batch keeps the latest of its steps (k_finalize)
+  if (blockIdx.y + (int64_t)cap < gridDim.y) return;
   const ReplicaParams<R> &p = reps[r];
-  const int64_t step = *step_ptr + step_off;
-  block_sum_rows(partials, p.tile0, p.tile0 + p.ntiles, tot);
+  const int64_t step = *step_ptr + step_off + blockIdx.y;
+  block_sum_rows(partials + blockIdx.y * pstride, p.tile0, p.tile0 + p.ntiles, tot);
   __syncthreads();
   if (threadIdx.x == 0) {
     double *row = series + ((int64_t)r * cap + step % cap) * kSeriesStride;
@@ -204,18 +207,18 @@ hipError_t launch_ensemble_step(int storage, bool general, const void *reps,
 }
 
 hipError_t launch_ensemble_finalize(int storage, const void *reps, int nrep,
-                                    const double *partials, double *series,
-                                    int cap, int64_t *step_ptr, int step_off, int bump,
+                                    const double *partials, int64_t pstride, int count,
+                                    double *series, int cap, int64_t *step_ptr, int step_off, int bump,
                                     double *mass0, bool stats, hipStream_t stream) {
   if (stats) {
     if (storage == kF64)
-      hipLaunchKernelGGL(k_ensemble_reduce<double>, dim3(nrep), dim3(256), 0, stream,
+      hipLaunchKernelGGL(k_ensemble_reduce<double>, dim3(nrep, count), dim3(256), 0, stream,
                          static_cast<const ReplicaParams<double> *>(reps), partials,
-                         series, cap, step_ptr, step_off, mass0);
+                         pstride, series, cap, step_ptr, step_off, mass0);
     else
-      hipLaunchKernelGGL(k_ensemble_reduce<float>, dim3(nrep), dim3(256), 0, stream,
+      hipLaunchKernelGGL(k_ensemble_reduce<float>, dim3(nrep, count), dim3(256), 0, stream,
                          static_cast<const ReplicaParams<float> *>(reps), partials,
-                         series, cap, step_ptr, step_off, mass0);
+                         pstride, series, cap, step_ptr, step_off, mass0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -218,8 +218,8 @@ hipError_t launch_ensemble_step(int storage, bool general, const void *reps,
                                 const int64_t *step_ptr, int step_off, double *partials,
                                 hipStream_t stream);
 hipError_t launch_ensemble_finalize(int storage, const void *reps, int nrep,
-                                    const double *partials, double *series,
-                                    int cap, int64_t *step_ptr, int step_off, int bump,
+                                    const double *partials, int64_t pstride, int count,
+                                    double *series, int cap, int64_t *step_ptr, int step_off, int bump,
                                     double *mass0, bool stats, hipStream_t stream);
 
 }  // namespace cmf
