@@ -13,9 +13,13 @@
 
 #include <hipfft/hipfft.h>
 
+#include <condition_variable>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "../../include/cmflb.h"
@@ -743,6 +747,144 @@ int run_fused(cmf_lattice *L, int n) {
   return CMF_OK;
 }
 
+// Copies of device arrays into the caller's pageable memory.  The runtime's
+// own copy moves them through its staging buffers on one thread, 17 GB/s into
+// memory that has been written before and 10 into fresh pages (a numpy array),
+// against 56 GB/s of the link to pinned memory.  Large arrays therefore go
+// through a ring of pinned chunks that kFetchThreads threads empty into the
+// caller's array, whose page faults they share (57 MB into a new numpy array 5.8 ->
+// 2.2 ms, 453 MB 45 -> 13; pinning the ring, for the length of the call, takes
+// 0.3).
+constexpr size_t kFetchChunk = (size_t)4 << 20;
+constexpr int kFetchSlots = 6, kFetchThreads = 4;
+
+struct FetchRing {
+  char *pin = nullptr;
+  hipEvent_t ready[kFetchSlots] = {};
+  ~FetchRing() {
+    for (auto &e : ready)
+      if (e) (void)hipEventDestroy(e);
+    if (pin) (void)hipHostFree(pin);
+  }
+  bool init() {
+    bool ok = hipHostMalloc((void **)&pin, kFetchSlots * kFetchChunk, hipHostMallocDefault) == hipSuccess;
+    for (auto &e : ready) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+  }
+};
+
+// chunks 0 .. n - 1 in order: copies enqueued by this thread, emptied by the
+// others; chunk c uses slot c mod kFetchSlots once chunk c - kFetchSlots is out
+hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s, FetchRing &ring,
+                        int device) {
+  const int64_t n = (int64_t)((bytes + kFetchChunk - 1) / kFetchChunk);
+  std::mutex mu;
+  std::condition_variable cv;
+  int64_t issued = 0, taken = 0;
+  std::vector<char> out(n, 0);
+  hipError_t err = hipSuccess;  // all guarded by mu
+  auto size_of = [&](int64_t c) {
+    const size_t at = (size_t)c * kFetchChunk;
+    return bytes - at < kFetchChunk ? bytes - at : kFetchChunk;
+  };
+  auto work = [&]() {
+    hipError_t e = hipSetDevice(device);
+    for (;;) {
+      std::unique_lock<std::mutex> lk(mu);
+      if (e != hipSuccess && err == hipSuccess) err = e;
+      if (err != hipSuccess || taken == n) break;
+      const int64_t c = taken++;
+      cv.wait(lk, [&] { return issued > c || err != hipSuccess; });
+      if (err != hipSuccess) break;
+      lk.unlock();
+      e = hipEventSynchronize(ring.ready[c % kFetchSlots]);
+      if (e == hipSuccess)
+        memcpy(dst + (size_t)c * kFetchChunk, ring.pin + (size_t)(c % kFetchSlots) * kFetchChunk, size_of(c));
+      lk.lock();
+      out[c] = 1;
+      if (e != hipSuccess && err == hipSuccess) err = e;
+      lk.unlock();
+      cv.notify_all();
+    }
+    cv.notify_all();
+  };
+  std::vector<std::thread> threads;
+  threads.reserve(kFetchThreads);
+  try {
+    for (int t = 0; t < kFetchThreads; ++t) threads.emplace_back(work);
+  } catch (const std::system_error &) {
+    // fewer threads, or none: the copies below need at least one
+  }
+  if (threads.empty()) return hipErrorOutOfMemory;
+  for (int64_t c = 0; c < n; ++c) {
+    {
+      std::unique_lock<std::mutex> lk(mu);
+      cv.wait(lk, [&] { return err != hipSuccess || c < kFetchSlots || out[c - kFetchSlots]; });
+      if (err != hipSuccess) break;
+    }
+    const int slot = (int)(c % kFetchSlots);
+    hipError_t e = hipMemcpyAsync(ring.pin + (size_t)slot * kFetchChunk, src + (size_t)c * kFetchChunk, size_of(c),
+                                  hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipEventRecord(ring.ready[slot], s);
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      if (e != hipSuccess) err = e;
+      issued = c + 1;
+    }
+    cv.notify_all();
+    if (e != hipSuccess) break;
+  }
+  for (auto &t : threads) t.join();
+  (void)hipStreamSynchronize(s);  // no copy into the ring outlives it
+  return err;
+}
+
+// `bytes` from device memory at src to dst, after the work already on s;
+// returns when they are there.
+hipError_t fetch(void *dst, const void *src, size_t bytes, hipStream_t s) {
+  if (bytes >= 2 * kFetchChunk) {
+    FetchRing ring;
+    int device = 0;
+    if (ring.init() && hipGetDevice(&device) == hipSuccess) {
+      try {
+        const hipError_t e = fetch_chunks((char *)dst, (const char *)src, bytes, s, ring, device);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();
+      } catch (const std::bad_alloc &) {
+      }
+    }
+  }
+  const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+  const hipError_t w = hipStreamSynchronize(s);
+  return e != hipSuccess ? e : w;
+}
+
+// Rows of steps [first, step), at most cap of them, from a series ring on the
+// device: the run up to the ring's end and the one from its start, or, of a
+// small ring, all of it (a copy takes 6 us, a larger one hardly more).
+hipError_t copy_series(const double *series, int cap, int64_t first, int64_t step,
+                       std::vector<double> &rows) {
+  rows.resize((size_t)(step - first) * kSeriesStride);
+  if (step > first && first % cap + step - first > cap && cap <= 512) {
+    std::vector<double> ring((size_t)cap * kSeriesStride);
+    const hipError_t e = hipMemcpy(ring.data(), series, sizeof(double) * ring.size(), hipMemcpyDeviceToHost);
+    for (int64_t s = first; s < step && e == hipSuccess; ++s)
+      memcpy(rows.data() + (s - first) * kSeriesStride, ring.data() + (s % cap) * kSeriesStride,
+             sizeof(double) * kSeriesStride);
+    return e;
+  }
+  for (int64_t s = first; s < step;) {
+    const int64_t at = s % cap, n = step - s < cap - at ? step - s : cap - at;
+    const hipError_t e = hipMemcpy(rows.data() + (s - first) * kSeriesStride,
+                                   series + at * kSeriesStride,
+                                   sizeof(double) * kSeriesStride * n, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    s += n;
+  }
+  return hipSuccess;
+}
+
 void release(cmf_lattice *L) {
   if (!L) return;
   if (L->stream) (void)hipStreamSynchronize(L->stream);
@@ -1085,8 +1227,7 @@ int cmf_get_populations(cmf_lattice *L, double *f) {
   if (hipMalloc((void **)&df, bytes) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_get_state(L->q, L->storage, conv(L), L->buf[L->parity], df, L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  if (e == hipSuccess) e = hipMemcpy(f, df, bytes, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = fetch(f, df, bytes, L->stream);
   (void)hipFree(df);
   if (e != hipSuccess) return fail(CMF_EHIP, "get_populations failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -1245,6 +1386,7 @@ int cmf_sk_reset(cmf_lattice *L, int32_t nbins) {
     if (L->sk_out) (void)hipFree(L->sk_out);
     L->sk_off = nullptr;
     L->sk_out = nullptr;
+    int32_t *counts = nullptr;
     if (hipMalloc((void **)&L->sk_off, sizeof(int64_t) * (nbins + 1)) != hipSuccess ||
         hipMalloc((void **)&L->sk_out, sizeof(double) * 6 * nbins * (1 + kSkParts)) != hipSuccess ||
         hipMalloc((void **)&counts, sizeof(int32_t) * kSkChunks * nbins) != hipSuccess)
@@ -1389,7 +1531,6 @@ int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, in
     (void)apply_launch(L, block0, grid0, L->amp, L->scale);
     return rc;
   }
-    int32_t *counts = nullptr;
   size_t best = 0;
   for (size_t k = 1; k < done.size(); ++k)
     if (done[k].ms_per_step < done[best].ms_per_step) best = k;
@@ -1439,14 +1580,8 @@ int cmf_stats(cmf_lattice *L, cmf_moments *out, int64_t cap, int64_t *n_out) {
   int64_t first = L->read_step;
   if (step - first > L->cap) first = step - L->cap;
   if (step - first > cap) first = step - cap;
-  std::vector<double> ring((size_t)L->cap * kSeriesStride);
-  if (step > first)
-    HIP_TRY(hipMemcpy(ring.data(), L->series, sizeof(double) * ring.size(),
-                      hipMemcpyDeviceToHost));
-  std::vector<double> rows((size_t)(step - first) * kSeriesStride);
-  for (int64_t s = first; s < step; ++s)
-    memcpy(rows.data() + (s - first) * kSeriesStride,
-           ring.data() + (s % L->cap) * kSeriesStride, sizeof(double) * kSeriesStride);
+  std::vector<double> rows;
+  HIP_TRY(copy_series(L->series, L->cap, first, step, rows));
   bool bad = false;
   for (int64_t s = first; s < step; ++s) {
     const double *r = rows.data() + (s - first) * kSeriesStride;
@@ -1486,9 +1621,8 @@ int cmf_get_macro(cmf_lattice *L, double *rho, double *u) {
   if (hipMalloc((void **)&d, bytes) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_macro(L->q, L->storage, conv(L), L->buf[L->parity], d, d + L->N, L->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-  if (e == hipSuccess && rho) e = hipMemcpy(rho, d, sizeof(double) * L->N, hipMemcpyDeviceToHost);
-  if (e == hipSuccess && u) e = hipMemcpy(u, d + L->N, sizeof(double) * 3 * L->N, hipMemcpyDeviceToHost);
+  if (e == hipSuccess && rho) e = fetch(rho, d, sizeof(double) * L->N, L->stream);
+  if (e == hipSuccess && u) e = fetch(u, d + L->N, sizeof(double) * 3 * L->N, L->stream);
   (void)hipFree(d);
   if (e != hipSuccess) return fail(CMF_EHIP, "get_macro failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -1892,7 +2026,7 @@ int ens_build_tiles(cmf_ensemble *E, int spt9, int spt3d) {
     int32_t *map = nullptr;
     double *parts = nullptr;
     if (hipMalloc((void **)&map, sizeof(int32_t) * nt) != hipSuccess ||
-        hipMalloc((void **)&parts, 2 * sizeof(double) * kPartStride * nt) != hipSuccess) {
+        hipMalloc((void **)&parts, sizeof(double) * kPartStride * rows) != hipSuccess) {
       if (map) (void)hipFree(map);
       return fail(CMF_ENOMEM, "allocation of the tile map (%d tiles) failed", nt);
     }
@@ -1901,7 +2035,9 @@ int ens_build_tiles(cmf_ensemble *E, int spt9, int spt3d) {
     E->d_tile_rep = map;
     E->partials = parts;
     E->tiles_cap = nt;
+    E->parts_cap = rows;
   }
+  E->stat_batch = K;
   for (int r = 0; r < E->n; ++r) {
     E->reps[r].tile0 = tile0[r];
     E->reps[r].ntiles = ntl[r];
@@ -2035,9 +2171,7 @@ int cmf_ensemble_create(const cmf_desc *descs, int32_t n, void *hip_stream, cmf_
 }
 
 int cmf_ensemble_destroy(cmf_ensemble *E) {
-    E->parts_cap = rows;
   if (!E) return fail(CMF_EINVAL, "ensemble is NULL");
-  E->stat_batch = K;
   ens_release(E);
   return CMF_OK;
 }
@@ -2190,8 +2324,7 @@ int cmf_ensemble_get_populations(cmf_ensemble *E, int32_t index, double *f) {
   double *df = nullptr;
   if (hipMalloc((void **)&df, bytes) != hipSuccess) return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_get_state(rp.desc.q, E->storage, rp.cp, ens_replica_buffer(E, index), df, E->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(E->stream);
-  if (e == hipSuccess) e = hipMemcpy(f, df, bytes, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = fetch(f, df, bytes, E->stream);
   (void)hipFree(df);
   if (e != hipSuccess) return fail(CMF_EHIP, "ensemble get_populations failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -2292,13 +2425,11 @@ int cmf_ensemble_stats(cmf_ensemble *E, int32_t index, cmf_moments *out, int64_t
   int64_t first = E->read_step[index];
   if (step - first > E->cap) first = step - E->cap;
   if (step - first > cap) first = step - cap;
-  std::vector<double> ring((size_t)E->cap * kSeriesStride);
-  if (step > first)
-    HIP_TRY(hipMemcpy(ring.data(), E->series + (size_t)index * E->cap * kSeriesStride,
-                      sizeof(double) * ring.size(), hipMemcpyDeviceToHost));
+  std::vector<double> rows;
+  HIP_TRY(copy_series(E->series + (size_t)index * E->cap * kSeriesStride, E->cap, first, step, rows));
   bool bad = false;
   for (int64_t s = first; s < step; ++s) {
-    const double *r = ring.data() + (s % E->cap) * kSeriesStride;
+    const double *r = rows.data() + (s - first) * kSeriesStride;
     cmf_moments &m = out[s - first];
     m.step = r[0];
     m.sum_rho = r[1];
