@@ -194,13 +194,15 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1,
   return U4{c0, c1, c2, c3};
 }
 
-// Box-Muller pair from two Philox words (a -> radius, b -> angle), times a
-// scale s: (z0, z1) = s (r cos theta, r sin theta).  The FP32 and FP64 step
-// kernels pass the site's noise amplitude, which then costs one multiply
-// per pair of modes instead of one per mode.
+// Box-Muller pair of two Philox words (a -> radius, b -> angle) times a scale f,
+// z0 = f r cos, z1 = f r sin, f r formed first; and its parts r, c = cos and s
+// = sin, which do not depend on the scale: the same values.
 template <typename R>
-__device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, R s, R &z0,
-                                           R &z1);
+__device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, R f, R &z0, R &z1);
+template <typename R>
+__device__ __forceinline__ void box_muller_parts(uint32_t a, uint32_t b, R &r, R &c, R &s);
+template <typename R>
+__device__ __forceinline__ R scaled_radius(R r, R f);
 
 // FP32: the hardware transcendentals.  v_log_f32 gives log2, so
 // r = sqrt(-2 ln u1) = sqrt(2 ln 2) sqrt(-log2 u1); v_sin_f32 / v_cos_f32
@@ -211,12 +213,27 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, R s, R &z0,
 // |eta_fp32 - eta| <= 1.2e-6; the form used here rounds the factor
 // sqrt(2 ln 2) s separately (one more rounding of r, 6e-8 relative).
 template <>
-__device__ __forceinline__ void box_muller<float>(uint32_t a, uint32_t b, float s,
-                                                  float &z0, float &z1) {
+__device__ __forceinline__ float scaled_radius<float>(float r, float f) {
+  return r * (f * 1.17741002f);
+}
+template <>
+__device__ __forceinline__ void box_muller_parts<float>(uint32_t a, uint32_t b, float &r, float &c,
+                                                        float &s) {
   // ((a >> 8) + 1) 2^-24 as one multiply-add of exact operands (exact)
   const float u1 = __builtin_fmaf((float)(a >> 8), 0x1p-24f, 0x1p-24f);  // (0, 1]
   const float u2 = (float)(b >> 8) * 0x1p-24f;         // [0, 1), exact
-  const float r = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1)) * (s * 1.17741002f);
+  r = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
+  c = __builtin_amdgcn_cosf(u2);
+  s = __builtin_amdgcn_sinf(u2);
+}
+// (written out: the order of the operations decides which registers the
+// 16-bit kernels need, and with them how many of their waves fit)
+template <>
+__device__ __forceinline__ void box_muller<float>(uint32_t a, uint32_t b, float f, float &z0,
+                                                  float &z1) {
+  const float u1 = __builtin_fmaf((float)(a >> 8), 0x1p-24f, 0x1p-24f);
+  const float u2 = (float)(b >> 8) * 0x1p-24f;
+  const float r = scaled_radius<float>(__builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1)), f);
   z0 = r * __builtin_amdgcn_cosf(u2);
   z1 = r * __builtin_amdgcn_sinf(u2);
 }
@@ -308,44 +325,111 @@ __device__ __forceinline__ void turn(uint32_t t, double &sn, double &cs) {
 }
 
 template <>
-__device__ __forceinline__ void box_muller<double>(uint32_t a, uint32_t b, double s,
-                                                   double &z0, double &z1) {
-  double sn, cs;
-  const double r = root(minus_two_log((a >> 8) + 1u)) * s;
-  turn(b >> 8, sn, cs);
-  z0 = r * cs;
-  z1 = r * sn;
+__device__ __forceinline__ double scaled_radius<double>(double r, double f) {
+  return r * f;
+}
+template <>
+__device__ __forceinline__ void box_muller_parts<double>(uint32_t a, uint32_t b, double &r,
+                                                         double &c, double &s) {
+  r = root(minus_two_log((a >> 8) + 1u));
+  turn(b >> 8, s, c);
+}
+template <>
+__device__ __forceinline__ void box_muller<double>(uint32_t a, uint32_t b, double f, double &z0,
+                                                   double &z1) {
+  double r, c, s;
+  box_muller_parts<double>(a, b, r, c, s);
+  r = scaled_radius<double>(r, f);
+  z0 = r * c;
+  z1 = r * s;
 }
 
-// The NNOISE normals of one site and step, eta[n] for mode FIRST_NOISY + n.
+// The NNOISE normals of one site and step, eta[n] for mode FIRST_NOISY + n, in
+// two steps: draw() takes everything that does not depend on the site's state,
+// so that a kernel can draw while the site's populations are on their way, and
+// scaled() multiplies by the site's amplitude.
 // Counter (site, step mod 2^32, replica, block + 2^8 floor(step / 2^32)):
 // the block index takes 8 bits, so the counters of all steps below 2^56
 // are distinct, and steps below 2^32 keep the plain (site, step, replica,
 // block) counter.  The step is wave-uniform, so its two words cost scalar
 // operations only.
-// scale: every normal comes out multiplied by it (1 for the normals
-// themselves).
-template <class L, typename R>
-__device__ __forceinline__ void site_normals(uint32_t site, uint64_t step,
-                                             uint32_t replica, uint32_t k0,
-                                             uint32_t k1, R scale, R *eta) {
-  const uint32_t step_lo = (uint32_t)step;
-  const uint32_t blk_hi = (uint32_t)(step >> 32) << 8;
+// UNIT: the scale is 1, and draw() forms the normals themselves.  (Otherwise
+// FP32 could keep the products of radius and angle functions, 91 instead of 101
+// registers on D3Q27, for one multiplication more per pair: 256^3 620 against
+// 614 us, the ensemble 958 against 943.)
+template <class L, typename R, bool UNIT>
+struct Normals {
+  static constexpr int PAIRS = (L::NNOISE + 1) / 2;
+  R r[PAIRS], c[PAIRS], s[PAIRS];
+  __device__ __forceinline__ void draw(uint32_t site, uint64_t step, uint32_t replica, uint32_t k0,
+                                       uint32_t k1) {
+    const uint32_t step_lo = (uint32_t)step;
+    const uint32_t blk_hi = (uint32_t)(step >> 32) << 8;
 #pragma unroll
-  for (int blk = 0; blk < L::NBLOCKS; ++blk) {
-    const U4 w = philox4x32_10(site, step_lo, replica, (uint32_t)blk | blk_hi, k0, k1);
-    const int n0 = 4 * blk;
-    R a, b;
-    box_muller<R>(w.x, w.y, scale, a, b);
-    if (n0 < L::NNOISE) eta[n0] = a;
-    if (n0 + 1 < L::NNOISE) eta[n0 + 1] = b;
-    if (n0 + 2 < L::NNOISE) {
-      R c, d;
-      box_muller<R>(w.z, w.w, scale, c, d);
-      eta[n0 + 2] = c;
-      if (n0 + 3 < L::NNOISE) eta[n0 + 3] = d;
+    for (int blk = 0; blk < L::NBLOCKS; ++blk) {
+      const U4 w = philox4x32_10(site, step_lo, replica, (uint32_t)blk | blk_hi, k0, k1);
+      pair(2 * blk, w.x, w.y);
+      if (2 * blk + 1 < PAIRS) pair(2 * blk + 1, w.z, w.w);
     }
   }
+  __device__ __forceinline__ void scaled(R scale, R *eta) const {
+#pragma unroll
+    for (int n = 0; n < L::NNOISE; ++n) {
+      const R part = n % 2 ? s[n / 2] : c[n / 2];
+      eta[n] = UNIT ? part : scaled_radius<R>(r[n / 2], scale) * part;
+    }
+  }
+
+ private:
+  __device__ __forceinline__ void pair(int p, uint32_t a, uint32_t b) {
+    box_muller_parts<R>(a, b, r[p], c[p], s[p]);
+    if constexpr (UNIT) {
+      const R f = scaled_radius<R>(r[p], R(1));
+      c[p] *= f;
+      s[p] *= f;
+    }
+  }
+};
+
+// The same normals drawn when the amplitude is known, block by block; P has
+// the fields replica, key0 and key1.
+template <class L, typename R, bool UNIT, class P>
+struct LateNormals {
+  const P &p;
+  uint32_t site;
+  uint64_t step;
+  __device__ __forceinline__ void scaled(R scale, R *eta) const {
+    const uint32_t step_lo = (uint32_t)step;
+    const uint32_t blk_hi = (uint32_t)(step >> 32) << 8;
+#pragma unroll
+    for (int blk = 0; blk < L::NBLOCKS; ++blk) {
+      const U4 w = philox4x32_10(site, step_lo, p.replica, (uint32_t)blk | blk_hi, p.key0, p.key1);
+      const int n0 = 4 * blk;
+      const R f = UNIT ? R(1) : scale;
+      R z0, z1;
+      box_muller<R>(w.x, w.y, f, z0, z1);
+      if (n0 < L::NNOISE) eta[n0] = z0;
+      if (n0 + 1 < L::NNOISE) eta[n0 + 1] = z1;
+      if (n0 + 2 < L::NNOISE) {
+        R z2, z3;
+        box_muller<R>(w.z, w.w, f, z2, z3);
+        eta[n0 + 2] = z2;
+        if (n0 + 3 < L::NNOISE) eta[n0 + 3] = z3;
+      }
+    }
+  }
+};
+
+struct NoiseKey {
+  uint32_t replica, key0, key1;
+};
+
+// all of them at once, unscaled
+template <class L, typename R>
+__device__ __forceinline__ void site_normals(uint32_t site, uint64_t step, uint32_t replica,
+                                             uint32_t k0, uint32_t k1, R *eta) {
+  const NoiseKey key{replica, k0, k1};
+  LateNormals<L, R, true, NoiseKey>{key, site, step}.scaled(R(1), eta);
 }
 
 // ---------------------------------------------------------------------------

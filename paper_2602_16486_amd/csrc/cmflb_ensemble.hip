@@ -69,17 +69,18 @@ __device__ __forceinline__ void ensemble_site(__amdgpu_buffer_rsrc_t rs, __amdgp
   }
   const uint32_t sb = us * B;
   const uint32_t popb = (uint32_t)p.pitch * B;
-  R d[L::Q];
+  Pulled<L, S, R> f{p.scale};
 #pragma unroll
   for (int i = 0; i < L::Q; ++i) {
     const uint32_t voff = sb + dx[L::cx[i] + 1] + dy[L::cy[i] + 1] + dz[L::cz[i] + 1];
-    const float sc = p.scale[weight_class<L>(i)];
     if (L::cx[i] == 0 && L::cy[i] == 0 && L::cz[i] == 0)
-      d[i] = ST::from_bits(buf_load<S, true>(rs, voff, (uint32_t)i * popb), sc);
+      f.keep(i, buf_load<S, true>(rs, voff, (uint32_t)i * popb));
     else
-      d[i] = ST::from_bits(buf_load<S, false>(rs, voff, (uint32_t)i * popb), sc);
+      f.keep(i, buf_load<S, false>(rs, voff, (uint32_t)i * popb));
   }
-  collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, us, step, acc);
+  const auto normals = f.normals(p, us, step);
+  R *d = f.d;
+  collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, acc);
 #pragma unroll
   for (int i = 0; i < L::Q; ++i)
     buf_store<S, true>(ST::to_bits(d[i], p.iscale[weight_class<L>(i)]), rd, sb, (uint32_t)i * popb);

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void k_noise(uint32_t key0, uint32_t key1,
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   R eta[L::NNOISE];
-  site_normals<L, R>((uint32_t)(site0 + k), step, replica, key0, key1, R(1), eta);
+  site_normals<L, R>((uint32_t)(site0 + k), step, replica, key0, key1, eta);
   for (int v = 0; v < L::Q; ++v)
     out[k * L::Q + v] =
         v < L::FIRST_NOISY ? 0.0 : (double)eta[v - L::FIRST_NOISY];

@@ -112,10 +112,8 @@ __device__ __forceinline__ bool finite4(R a, R b, R c, R d) {
 // constant, instead of being kept per mode in scalar registers (which then
 // spill into vector lanes); the wider storages, bound by HBM, measured
 // slightly faster with the per-mode values.
-template <class L, typename R, bool GENERAL, bool LEAN, class P, class A>
-__device__ __forceinline__ void collide_tensor(R *d, const P &p,
-                                               uint32_t site, uint64_t step,
-                                               A &acc) {
+template <class L, typename R, bool GENERAL, bool LEAN, class P, class NM, class A>
+__device__ __forceinline__ void collide_tensor(R *d, const P &p, const NM &normals, A &acc) {
   constexpr int Q = L::Q;
   // step 1: rho = rho0 + sum d, rho u = sum c d (eq. macro).  D3Q27 forms
   // them from per-row partial sums (sum and difference along x of each
@@ -174,7 +172,7 @@ __device__ __forceinline__ void collide_tensor(R *d, const P &p,
   const R a1 = p.amp1 * sqrt(rho);
   R eta[L::NNOISE];
   if (p.noise) {
-    site_normals<L, R>(site, step, p.replica, p.key0, p.key1, LEAN ? R(1) : a1, eta);
+    normals.scaled(a1, eta);
   } else {
 #pragma unroll
     for (int n = 0; n < L::NNOISE; ++n) eta[n] = R(0);
@@ -308,9 +306,8 @@ __device__ __forceinline__ void collide_tensor(R *d, const P &p,
 // same steps with k = N(u) r and f* = M^-1 N(u)^-1 k* (cmflb_d3q19.h).  With
 // the paper's rates only k_7..k_9 = r_7..r_9 - rho u_a u_b are needed
 // (M_7 = c_x c_y, M_8 = c_y c_z, M_9 = c_x c_z); k_eq = (rho, 0, ..., 0).
-template <typename R, bool GENERAL, bool LEAN, class P, class A>
-__device__ __forceinline__ void collide_d3q19(R *d, const P &p, uint32_t site,
-                                              uint64_t step, A &acc) {
+template <typename R, bool GENERAL, bool LEAN, class P, class NM, class A>
+__device__ __forceinline__ void collide_d3q19(R *d, const P &p, const NM &normals, A &acc) {
   using L = D3Q19;
   R r[19];
   d3q19::raw_moments(d, r);
@@ -324,7 +321,7 @@ __device__ __forceinline__ void collide_d3q19(R *d, const P &p, uint32_t site,
   const R a1 = p.amp1 * sqrt(rho);  // as in collide_tensor
   R eta[L::NNOISE];
   if (p.noise) {
-    site_normals<L, R>(site, step, p.replica, p.key0, p.key1, LEAN ? R(1) : a1, eta);
+    normals.scaled(a1, eta);
   } else {
 #pragma unroll
     for (int n = 0; n < L::NNOISE; ++n) eta[n] = R(0);
@@ -377,14 +374,61 @@ __device__ __forceinline__ void collide_d3q19(R *d, const P &p, uint32_t site,
   d3q19::populations(k, d);
 }
 
-template <class L, typename R, bool GENERAL, bool LEAN, class P, class A>
-__device__ __forceinline__ void collide_site(R *d, const P &p, uint32_t site,
-                                             uint64_t step, A &acc) {
+template <class L, typename R, bool GENERAL, bool LEAN, class P, class NM, class A>
+__device__ __forceinline__ void collide_site(R *d, const P &p, const NM &normals, A &acc) {
   if constexpr (L::Q == 19)
-    collide_d3q19<R, GENERAL, LEAN>(d, p, site, step, acc);
+    collide_d3q19<R, GENERAL, LEAN>(d, p, normals, acc);
   else
-    collide_tensor<L, R, GENERAL, LEAN>(d, p, site, step, acc);
+    collide_tensor<L, R, GENERAL, LEAN>(d, p, normals, acc);
 }
+
+// Whether a site's normals are drawn before its populations are used.  The
+// draw is a block of its own behind a scalar branch, across which the compiler
+// moves neither loads nor their waits: placed first, one wave's noise covers
+// its own loads, for the registers that hold the drawn parts meanwhile.  FP32
+// steps gain (us, one machine: D3Q27 50^3 16.5 -> 15.7, 128^3 91 -> 87, D3Q19 256^3
+// 431 -> 414, D2Q9 4096^2 223 -> 216, the 320-replica ensemble 955 -> 944), but for
+// D3Q27 lattices well beyond the last-level cache, which wait for HBM with
+// either order and keep five waves per SIMD instead of four (256^3 612 against
+// 619 on one machine, 614 against 610 and 624 against 613 on others).  FP64 ones
+// gain too (D3Q19 128^3 132 -> 125, D2Q9 1024^2 33.1 -> 31.8) but on D3Q27, where 216
+// instead of 160 registers leave two waves (256^3 1379 -> 1417).  16-bit steps
+// issue in every cycle and lose the waves (D3Q27 256^3 FP16 431 -> 444).
+template <class L, typename S>
+constexpr bool kDrawFirst = sizeof(S) == 4 || (sizeof(S) == 8 && L::Q != 27);
+// largest single D3Q27 FP32 lattice that draws first, in sites
+constexpr int64_t kDrawFirstSites = (int64_t)1 << 22;
+
+// The populations of a site between their loads and the collision, and its
+// normals.  keep(i, bits) takes population i as it is loaded, normals() draws
+// (or arranges to) and completes the deviations d.
+template <class L, typename S, typename R, bool DRAW_FIRST = kDrawFirst<L, S>>
+struct Pulled {
+  using bits_t = typename Store<S, R>::bits_t;
+  static constexpr bool UNIT = sizeof(S) == 2;
+  const float *scale;
+  bits_t raw[DRAW_FIRST ? L::Q : 1];
+  R d[L::Q];
+  __device__ __forceinline__ void keep(int i, bits_t b) {
+    if constexpr (DRAW_FIRST)
+      raw[i] = b;
+    else
+      d[i] = Store<S, R>::from_bits(b, scale[weight_class<L>(i)]);
+  }
+  template <class P>
+  __device__ __forceinline__ auto normals(const P &p, uint32_t site, uint64_t step) {
+    if constexpr (DRAW_FIRST) {
+      Normals<L, R, UNIT> n;
+      if (p.noise) n.draw(site, step, p.replica, p.key0, p.key1);
+#pragma unroll
+      for (int i = 0; i < L::Q; ++i)
+        d[i] = Store<S, R>::from_bits(raw[i], scale[weight_class<L>(i)]);
+      return n;
+    } else {
+      return LateNormals<L, R, UNIT, P>{p, site, step};
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------
 // block reduction of the statistics accumulators (fixed order)
@@ -490,11 +534,10 @@ __device__ __forceinline__ int wrap_sub(int a, int c, int n) {
 // every population row is a whole number of cache lines (then tiles, which
 // start at a row or at a multiple of 256 sites of a row, never share a
 // line of such a row).
-template <class L, typename S, typename R, bool NT_C0 = false>
-__device__ __forceinline__ void load_site(R *d, const S *__restrict__ src,
-                                          const float *scale, int nx, int ny,
-                                          int nz, int x, int y, int z) {
-  using ST = Store<S, R>;
+template <class L, typename S, bool NT_C0, class K>
+__device__ __forceinline__ void load_site(K keep, const S *__restrict__ src, int nx, int ny, int nz, int x,
+                                          int y, int z) {
+  using bits_t = typename Store<S, float>::bits_t;
   const uint32_t xs[3] = {(uint32_t)(x == nx - 1 ? 0 : x + 1), (uint32_t)x,
                           (uint32_t)(x == 0 ? nx - 1 : x - 1)};
   int64_t srow[3][3];
@@ -508,13 +551,13 @@ __device__ __forceinline__ void load_site(R *d, const S *__restrict__ src,
     }
 #pragma unroll
   for (int i = 0; i < L::Q; ++i) {
-    const S *base = src + pop_row_offset<L>(i, srow[L::cy[i] + 1][L::cz[i] + 1], nx);
-    const float sc = scale[weight_class<L>(i)];
+    const bits_t *base = reinterpret_cast<const bits_t *>(
+        src + pop_row_offset<L>(i, srow[L::cy[i] + 1][L::cz[i] + 1], nx));
     // (the condition is a compile-time constant once the loop is unrolled)
     if (NT_C0 && L::cx[i] == 0)
-      d[i] = ST::template load<true>(base + xs[1], sc);
+      keep(i, cmf_ld<true>(base + xs[1]));
     else
-      d[i] = ST::template load<false>(base + xs[L::cx[i] + 1], sc);
+      keep(i, cmf_ld<false>(base + xs[L::cx[i] + 1]));
   }
 }
 
@@ -536,11 +579,9 @@ __device__ __forceinline__ void store_site(const R *d, S *__restrict__ dst,
 // step (BUF): one resource per source plane z - c_z (its Q ny rows of nx
 // values, below 4 GiB), the row of population i of source row y - c_y as a
 // scalar byte offset, and one vector byte offset per x shift.
-template <class L, typename S, typename R, bool NT_C0>
-__device__ __forceinline__ void load_site_buf(R *d, const S *__restrict__ src,
-                                              const float *scale, int nx, int ny,
+template <class L, typename S, bool NT_C0, class K>
+__device__ __forceinline__ void load_site_buf(K keep, const S *__restrict__ src, int nx, int ny,
                                               int nz, int x, int y, int z) {
-  using ST = Store<S, R>;
   constexpr uint32_t B = sizeof(S);
   const int64_t plane = (int64_t)ny * L::Q * nx;
   const uint32_t pbytes = (uint32_t)(plane * B);
@@ -559,11 +600,10 @@ __device__ __forceinline__ void load_site_buf(R *d, const S *__restrict__ src,
 #pragma unroll
   for (int i = 0; i < L::Q; ++i) {
     const uint32_t soff = (ys[L::cy[i] + 1] * (uint32_t)L::Q + (uint32_t)pop_slot<L>(i)) * rowb;
-    const float sc = scale[weight_class<L>(i)];
     if (NT_C0 && L::cx[i] == 0)
-      d[i] = ST::from_bits(buf_load<S, true>(rs[L::cz[i] + 1], xs[1], soff), sc);
+      keep(i, buf_load<S, true>(rs[L::cz[i] + 1], xs[1], soff));
     else
-      d[i] = ST::from_bits(buf_load<S, false>(rs[L::cz[i] + 1], xs[L::cx[i] + 1], soff), sc);
+      keep(i, buf_load<S, false>(rs[L::cz[i] + 1], xs[L::cx[i] + 1], soff));
   }
 }
 
@@ -615,11 +655,11 @@ __device__ __forceinline__ void store_tile_stats(const A &acc, const P &p, doubl
 // values); otherwise workgroups stride over the tiles and accumulate in FP64.
 // BUF: buffer-addressed population accesses (every z plane of the buffer
 // below 4 GiB); otherwise 64-bit addresses.
-template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool BUF>
+// FIRST: normals before populations (kDrawFirst).
+template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool BUF, bool FIRST>
 __global__ __launch_bounds__(kMaxBlock) void k_step(
     const S *__restrict__ src, S *__restrict__ dst, const StepParams<R> p,
     const int64_t *__restrict__ step_ptr, int step_off, double *__restrict__ partials) {
-  constexpr int Q = L::Q;
   const uint64_t step = (uint64_t)(*step_ptr + step_off);
   const int BX = blockDim.x;
   const int nx = p.nx, ny = p.ny;
@@ -629,14 +669,17 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(
   for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
     const TileXY c = tile_coords(tile, p.nxb, ny, BX);
     if (c.x < nx) {
-      R d[Q];
+      Pulled<L, S, R, FIRST> f{p.scale};
+      auto keep = [&](int i, typename Store<S, R>::bits_t b) { f.keep(i, b); };
       if constexpr (BUF)
-        load_site_buf<L, S, R, NT>(d, src, p.scale, nx, ny, p.nz, c.x, c.y, c.z);
+        load_site_buf<L, S, NT>(keep, src, nx, ny, p.nz, c.x, c.y, c.z);
       else
-        load_site<L, S, R, NT>(d, src, p.scale, nx, ny, p.nz, c.x, c.y, c.z);
+        load_site<L, S, NT>(keep, src, nx, ny, p.nz, c.x, c.y, c.z);
       const int64_t row = (int64_t)c.y + (int64_t)ny * c.z;
       const int site = (int)(c.x + nx * row);
-      collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, (uint32_t)site, step, acc);
+      const auto normals = f.normals(p, (uint32_t)site, step);
+      R *d = f.d;
+      collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, acc);
       if constexpr (BUF)
         store_site_buf<L, S, R, NT>(d, dst, p.iscale, nx, ny, c.x, c.y, c.z);
       else
@@ -656,10 +699,9 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(
 // NT (population rows of whole cache lines): non-temporal accesses where a
 // tile covers whole rows, every access of the even step and the c_x = 0
 // accesses of the odd step.
-template <class L, typename S, typename R, bool NT, bool ODD>
-__device__ __forceinline__ void load_site_aa(R *d, const S *buf, const float *scale, int nx,
-                                             int ny, int nz, int x, int y, int z) {
-  using ST = Store<S, R>;
+template <class L, typename S, bool NT, bool ODD, class K>
+__device__ __forceinline__ void load_site_aa(K keep, const S *buf, int nx, int ny, int nz, int x,
+                                             int y, int z) {
   constexpr uint32_t B = sizeof(S);
   const int64_t plane = (int64_t)ny * L::Q * nx;
   const uint32_t pbytes = (uint32_t)(plane * B);
@@ -668,8 +710,7 @@ __device__ __forceinline__ void load_site_aa(R *d, const S *buf, const float *sc
     const __amdgpu_buffer_rsrc_t r = make_rsrc(buf + (int64_t)z * plane, pbytes);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i)
-      d[i] = ST::from_bits(buf_load<S, NT>(r, (uint32_t)x * B, ((uint32_t)y * L::Q + pop_slot<L>(i)) * rowb),
-                           scale[weight_class<L>(i)]);
+      keep(i, buf_load<S, NT>(r, (uint32_t)x * B, ((uint32_t)y * L::Q + pop_slot<L>(i)) * rowb));
   } else {
     __amdgpu_buffer_rsrc_t rs[3];
 #pragma unroll
@@ -686,11 +727,10 @@ __device__ __forceinline__ void load_site_aa(R *d, const S *buf, const float *sc
     for (int i = 0; i < L::Q; ++i) {
       const uint32_t soff =
           (ys[L::cy[i] + 1] * (uint32_t)L::Q + (uint32_t)pop_slot<L>(opposite<L>(i))) * rowb;
-      const float sc = scale[weight_class<L>(i)];
       if (NT && L::cx[i] == 0)
-        d[i] = ST::from_bits(buf_load<S, true>(rs[L::cz[i] + 1], xs[1], soff), sc);
+        keep(i, buf_load<S, true>(rs[L::cz[i] + 1], xs[1], soff));
       else
-        d[i] = ST::from_bits(buf_load<S, false>(rs[L::cz[i] + 1], xs[L::cx[i] + 1], soff), sc);
+        keep(i, buf_load<S, false>(rs[L::cz[i] + 1], xs[L::cx[i] + 1], soff));
     }
   }
 }
@@ -743,7 +783,6 @@ template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool
 __global__ __launch_bounds__(kMaxBlock) void k_step_aa(
     S *buf, const StepParams<R> p, const int64_t *__restrict__ step_ptr, int step_off,
     double *__restrict__ partials) {
-  constexpr int Q = L::Q;
   const uint64_t step = (uint64_t)(*step_ptr + step_off);
   const int BX = blockDim.x;
   const int nx = p.nx, ny = p.ny;
@@ -753,11 +792,15 @@ __global__ __launch_bounds__(kMaxBlock) void k_step_aa(
   for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
     const TileXY c = tile_coords(tile, p.nxb, ny, BX);
     if (c.x < nx) {
-      R d[Q];
-      load_site_aa<L, S, R, NT, ODD>(d, buf, p.scale, nx, ny, p.nz, c.x, c.y, c.z);
+      // (in place, D3Q27 draws late too: 256^3 FP32 644 against 651 us)
+      Pulled<L, S, R, kDrawFirst<L, S> && L::Q != 27> f{p.scale};
+      auto keep = [&](int i, typename Store<S, R>::bits_t b) { f.keep(i, b); };
+      load_site_aa<L, S, NT, ODD>(keep, buf, nx, ny, p.nz, c.x, c.y, c.z);
       const int64_t row = (int64_t)c.y + (int64_t)ny * c.z;
       const int site = (int)(c.x + nx * row);
-      collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, (uint32_t)site, step, acc);
+      const auto normals = f.normals(p, (uint32_t)site, step);
+      R *d = f.d;
+      collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, acc);
       store_site_aa<L, S, R, NT, ODD>(d, buf, p.iscale, nx, ny, p.nz, c.x, c.y, c.z);
     }
     if constexpr (ONE) break;
@@ -781,10 +824,18 @@ hipError_t shape(const StepParams<R> &p, const void *src, void *dst,
                  int block, hipStream_t stream) {
   auto go = [&](auto one, int nblocks, size_t lds) {
     constexpr bool ONE = decltype(one)::value;
+    if constexpr (MODE == kStreamPull && L::Q == 27 && sizeof(S) == 4) {
+      if ((int64_t)p.nx * p.ny * p.nz > kDrawFirstSites) {
+        hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF, false>), dim3(nblocks), dim3(block),
+                           lds, stream, static_cast<const S *>(src), static_cast<S *>(dst), p,
+                           step_ptr, step_off, partials);
+        return hipGetLastError();
+      }
+    }
     if constexpr (MODE == kStreamPull)
-      hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF>), dim3(nblocks), dim3(block), lds,
-                         stream, static_cast<const S *>(src), static_cast<S *>(dst), p, step_ptr,
-                         step_off, partials);
+      hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF, kDrawFirst<L, S>>), dim3(nblocks),
+                         dim3(block), lds, stream, static_cast<const S *>(src),
+                         static_cast<S *>(dst), p, step_ptr, step_off, partials);
     else
       hipLaunchKernelGGL((k_step_aa<L, S, R, G, NT, ONE, MODE == kStreamAAOdd>), dim3(nblocks),
                          dim3(block), lds, stream, static_cast<S *>(dst), p, step_ptr, step_off,

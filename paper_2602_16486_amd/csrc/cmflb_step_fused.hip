@@ -94,7 +94,8 @@ __global__ __launch_bounds__(1024) void k_step_fused(
       gx = gx < 0 ? gx + nx : gx >= nx ? gx - nx : gx;
       gy = gy < 0 ? gy + ny : gy >= ny ? gy - ny : gy;
       const int lidx = (ry + j) * RX + rx + j;  // in the first step's region
-      R d[Q];
+      // (FP64 draws when it collides: 64^2 without noise 1.51 against 1.58 us)
+      Pulled<L, S, R, sizeof(S) == 4> f{p.scale};
       if (j == 0) {
         const uint32_t xs[3] = {(uint32_t)wrap_sub(gx, -1, nx) * B, (uint32_t)gx * B,
                                 (uint32_t)wrap_sub(gx, 1, nx) * B};
@@ -102,18 +103,18 @@ __global__ __launch_bounds__(1024) void k_step_fused(
                                 (uint32_t)wrap_sub(gy, 1, ny) * Q * rowb};
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-          d[q] = ST::from_bits(buf_load<S, false>(rs, ys[L::cy[q] + 1] + xs[L::cx[q] + 1],
-                                                  (uint32_t)pop_slot<L>(q) * rowb),
-                               p.scale[weight_class<L>(q)]);
+          f.keep(q, buf_load<S, false>(rs, ys[L::cy[q] + 1] + xs[L::cx[q] + 1],
+                                       (uint32_t)pop_slot<L>(q) * rowb));
       } else {
         const auto *from = &lds.pop[(j & 1) ^ 1][0][lidx];
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-          d[q] = ST::from_bits(from[q * RX * Lds::RY - L::cy[q] * RX - L::cx[q]],
-                               p.scale[weight_class<L>(q)]);
+          f.keep(q, from[q * RX * Lds::RY - L::cy[q] * RX - L::cx[q]]);
       }
+      const auto normals = f.normals(p, (uint32_t)(gx + nx * gy), step0 + j);
+      R *d = f.d;
       SiteStats<R> st;
-      collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, (uint32_t)(gx + nx * gy), step0 + j, st);
+      collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, st);
       if (h > 0) {
         auto *to = &lds.pop[j & 1][0][lidx];
 #pragma unroll
