@@ -395,6 +395,38 @@ void class_scales(int q, int storage, const float *scale, float *cs, float *ics)
   }
 }
 
+// Tiles per z plane of a 3-D lattice whose tiles are runs of the plane's
+// sites, 0 where they are parts of a row.  A step of a 3-D box issues for most
+// of its time, and lanes beyond the end of a row issue like any other: a row
+// of 50 takes a wave of 64, one of 150 three.  Runs of sites leave no lane
+// idle but those of a plane's last tile, for some 25 more address operations
+// per site (a lane's row is a vector value).  us per step, rows -> runs: D3Q27
+// FP32 50^3 14.3 -> 12.0, 32 x 96 x 96 20.7 -> 17.5, 100^3 44.3 -> 40.8, FP16 100^3 40.0 ->
+// 34.6, FP64 50^3 20.6 -> 19.1; D3Q19 BF16 72 x 60 x 50 15.6 -> 11.9, FP32 in place
+// 150 x 144 x 160 98.7 -> 87.9.  Where rows waste less than kFlatGain the gain is within
+// the noise or lost (D3Q27 FP32 120^3 76.3 -> 77.1, 250 x 120 x 90 110.6 -> 111.9).  D3Q27 in FP32 waits for
+// HBM once a box has outgrown the last-level cache, and a tile that ends
+// inside a 32-byte sector has its ends written in two parts: then only rows of
+// whole sectors go in runs (200 x 200 x 160 278 -> 268; 150 x 144 x 160 145.4 -> 147.1).
+constexpr double kFlatGain = 1.1;
+constexpr int64_t kFlatCached = (int64_t)1 << 21;  // sites
+int flat_plane_tiles(const cmf_desc &d, int block) {
+  const int64_t plane = (int64_t)d.nx * d.ny, b = (int64_t)storage_bytes(d.storage);
+  if (d.q == 9 || d.nx < 2 || d.nx > 8192 || plane * d.q * b >= (int64_t)1 << 32) return 0;
+  if (d.q == 27 && d.storage == kF32 && !(d.flags & CMF_FLAG_IN_PLACE) &&
+      plane * d.nz > kFlatCached && d.nx * b % 32 != 0)
+    return 0;
+  const int64_t flat = (plane + block - 1) / block;
+  const int64_t rows = (int64_t)((d.nx + block - 1) / block) * d.ny;
+  return kFlatGain * flat <= rows ? (int)flat : 0;
+}
+
+// Tiles of a lattice with workgroups of `block` threads.
+int tiles_for(const cmf_desc &d, int block) {
+  const int flat = flat_plane_tiles(d, block);
+  return (flat ? flat : (d.nx + block - 1) / block * d.ny) * d.nz;
+}
+
 // Step-kernel parameters of a lattice description with workgroups of
 // `block` threads.
 template <typename R>
@@ -404,8 +436,10 @@ void fill_params(const cmf_desc &d, const double *lambda, const double *amp, con
   p.nx = d.nx;
   p.ny = d.ny;
   p.nz = d.nz;
-  p.nxb = (d.nx + block - 1) / block;
-  p.ntiles = p.nxb * p.ny * p.nz;
+  const int flat = flat_plane_tiles(d, block);
+  p.nxb = flat ? flat : (d.nx + block - 1) / block;
+  p.ntiles = tiles_for(d, block);
+  p.flat = flat ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d.nx + 1) : 0;
   p.noise = d.kT > 0.0 ? 1 : 0;
   p.ncx = (d.nx + kCell - 1) / kCell;
   p.rho0 = (R)d.rho0;
@@ -486,20 +520,21 @@ bool lookup_tuned(const cmf_lattice *L, int *block, int *grid) {
   return true;
 }
 
-// Workgroup size of an untuned lattice: the one whose tiles cover a row with
+// Workgroup size of an untuned lattice: the one whose tiles cover the box with
 // the fewest lanes, weighted by what a lane costs in a workgroup of that size
 // (the start of a workgroup and its statistics are shared by its lanes).  One
 // tile per workgroup, D3Q27, us per step at 64 / 128 / 192 / 256 threads: nx =
 // 300 FP32 110 / 101 / 104 / 114, FP64 207 / 218 / 222 / 262; nx = 200 FP32 160 /
 // 159 / 175 / 119, FP64 317 / 314 / 412 / 309; nx = 160 FP32 147 / 162 / 138; nx =
 // 100 FP32 58 / 48.
-int default_block(int nx, int storage) {
-  const double cost[4] = {storage == kF64 ? 1.1 : 1.35, storage == kF64 ? 1.05 : 1.1, 1.1, 1.0};
+int default_block(const cmf_desc &d) {
+  const bool f64 = d.storage == kF64;
+  const double cost[4] = {f64 ? 1.1 : 1.35, f64 ? 1.05 : 1.1, 1.1, 1.0};
   int best = 0;
   double least = 0.0;
   for (int k = 0; k < 4; ++k) {
     const int b = 64 * (k + 1);
-    const double c = (double)((nx + b - 1) / b) * b * cost[k];
+    const double c = (double)tiles_for(d, b) * b * cost[k];
     if (!best || c < least) {
       best = b;
       least = c;
@@ -532,9 +567,7 @@ int choose_tile_rows(const cmf_lattice *L) {
   return 0;
 }
 
-int ntiles_for(const cmf_lattice *L, int block) {
-  return ((L->desc.nx + block - 1) / block) * L->desc.ny * L->desc.nz;
-}
+int ntiles_for(const cmf_lattice *L, int block) { return tiles_for(L->desc, block); }
 
 // Workgroups of an untuned lattice.  FP32 and FP64 3-D steps wait for memory:
 // one tile per workgroup (D3Q27 FP32 / FP64 us per step against 2 per CU:
@@ -1138,7 +1171,7 @@ int create_lattice(const cmf_desc *desc, void *hip_stream, void *ext, size_t ext
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, L->device) == hipSuccess && prop.multiProcessorCount > 0)
       L->cus = prop.multiProcessorCount;
-    int block = default_block(desc->nx, L->storage);
+    int block = default_block(*desc);
     int grid = default_grid(L, block);
     lookup_tuned(L, &block, &grid);
     const int be = env_int("CMF_BLOCK", 0), ge = env_int("CMF_GRID", 0);
@@ -1489,7 +1522,7 @@ int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, in
   }
   std::vector<int> blocks;
   for (int b = 64; b <= 256; b += 64)
-    if (b == 64 || b - 64 < L->desc.nx) blocks.push_back(b);
+    if (b == 64 || b - 64 < L->desc.nx || flat_plane_tiles(L->desc, b)) blocks.push_back(b);
   std::vector<cmf_launch> done;
   int rc = CMF_OK;
   const bool set0 = L->shape_set;

@@ -86,27 +86,12 @@ __device__ __forceinline__ void ensemble_site(__amdgpu_buffer_rsrc_t rs, __amdgp
     buf_store<S, true>(ST::to_bits(d[i], p.iscale[weight_class<L>(i)]), rd, sb, (uint32_t)i * popb);
 }
 
-// Workgroups are handed to the XCDs round-robin by id and every XCD has its
-// own L2.  Map workgroup b to a tile so that runs of kXcdChunk adjacent
-// tiles go to one XCD (chunk c to XCD c mod kXcds): two tiles that split a
-// lattice row, or that pull from each other's rows, then mostly meet in the
-// same L2, which merges the two parts of a shared cache line before it goes
-// to HBM; the chunks rotate over the XCDs, so tiles of different cost (D2Q9
-// and D3Q27 replicas) spread evenly.  A bijection on [0, n): the last
-// n mod (kXcds kXcdChunk) tiles keep their own ids.
-__device__ __forceinline__ int xcd_tile(int b, int n) {
-  constexpr int G = kXcds * kXcdChunk;
-  if (b >= n / G * G) return b;
-  const int j = b % kXcds, k = b / kXcds;
-  return ((k / kXcdChunk) * kXcds + j) * kXcdChunk + k % kXcdChunk;
-}
-
 template <typename S, typename R, bool GENERAL>
 __global__ __launch_bounds__(kEnsembleBlock) void k_ensemble_step(
     const S *__restrict__ src, S *__restrict__ dst,
     const ReplicaParams<R> *__restrict__ reps, const int32_t *__restrict__ tile_rep,
     const int64_t *__restrict__ step_ptr, int step_off, double *__restrict__ partials) {
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = xcd_tile<kXcdChunk>(blockIdx.x, gridDim.x);
   const ReplicaParams<R> &p = reps[tile_rep[tile]];
   const uint64_t step = (uint64_t)(*step_ptr + step_off);
   Acc acc;

@@ -35,8 +35,8 @@ constexpr int kCellPitch = kCell + 4;
 // so every field lives in scalar registers).
 template <typename R>
 struct StepParams {
-  int32_t nx, ny, nz, nxb;  // box and x-tiles per row
-  int32_t ntiles;           // nxb * ny * nz
+  int32_t nx, ny, nz, nxb;  // box and tiles per row (per plane when flat)
+  int32_t ntiles;           // nxb * ny * nz (nxb * nz when flat)
   int32_t noise;            // kT > 0
   int32_t cells;            // D2Q9: statistics in cell order (one-tile launches)
   int32_t ncx;              // statistics cells per lattice row
@@ -53,6 +53,9 @@ struct StepParams {
   // scalar registers
   float scale[4], iscale[4];
   uint32_t key0, key1, replica;
+  // 2^32 / nx + 1, to divide by nx, where tiles are runs of the sites of a z
+  // plane (see flat_plane_tiles); 0: tiles of a row
+  uint32_t flat;
 };
 
 // One replica of a batched ensemble as the ensemble kernel sees it (an
@@ -212,6 +215,11 @@ constexpr int kLineBytes = 128;
 constexpr int kXcds = 8;
 // adjacent ensemble tiles kept on one XCD
 constexpr int kXcdChunk = 8;
+// and of the tiles of a single lattice that are no whole rows (D3Q27 50^3 / 100^3 FP32,
+// D3Q19 in place 150 x 144 x 160 FP32, D3Q27 100^3 FP64: 13.0 / 43.6 / 93.6 / 109 us per
+// step in runs of 2 tiles, 12.9 / 41.7 / 92.2 / 108 of 8, 12.0 / 40.8 / 87.9 / 105 of 32;
+// without runs 150 x 144 x 160 D3Q27 FP32 took 174 against 147)
+constexpr int kFlatXcdChunk = 32;
 hipError_t launch_ensemble_step(int storage, bool general, const void *reps,
                                 const int32_t *tile_rep, int ntiles,
                                 const void *src, void *dst,

@@ -575,11 +575,32 @@ __device__ __forceinline__ void store_site(const R *d, S *__restrict__ dst,
   }
 }
 
+// Byte offsets, in a z plane's buffer, of the sites (x - c_x, y - c_y),
+// periodic, where the lanes of a wave are in several rows (FLAT): one vector
+// offset per shift in x and y (nine sums); population i is a scalar offset.
+template <class L, typename S>
+struct PlaneOffsets {
+  static constexpr uint32_t B = sizeof(S);
+  uint32_t rowb, xs[3], ys[3];
+
+  __device__ __forceinline__ PlaneOffsets(int nx, int ny, int x, int y)
+      : rowb((uint32_t)nx * B),
+        xs{(uint32_t)(x == nx - 1 ? 0 : x + 1) * B, (uint32_t)x * B,
+           (uint32_t)(x == 0 ? nx - 1 : x - 1) * B} {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) ys[a] = (uint32_t)wrap_sub(y, a - 1, ny) * (uint32_t)L::Q * rowb;
+  }
+  __device__ __forceinline__ uint32_t site(int cx, int cy) const { return ys[cy + 1] + xs[cx + 1]; }
+  __device__ __forceinline__ uint32_t population(int i) const {
+    return (uint32_t)pop_slot<L>(i) * rowb;
+  }
+};
+
 // Buffer-addressed forms of load_site / store_site for the single-lattice
 // step (BUF): one resource per source plane z - c_z (its Q ny rows of nx
-// values, below 4 GiB), the row of population i of source row y - c_y as a
-// scalar byte offset, and one vector byte offset per x shift.
-template <class L, typename S, bool NT_C0, class K>
+// values, below 4 GiB), and in tiles of a row the row of population i of source
+// row y - c_y as a scalar byte offset, one vector byte offset per x shift.
+template <class L, typename S, bool NT_C0, bool FLAT, class K>
 __device__ __forceinline__ void load_site_buf(K keep, const S *__restrict__ src, int nx, int ny,
                                               int nz, int x, int y, int z) {
   constexpr uint32_t B = sizeof(S);
@@ -590,6 +611,18 @@ __device__ __forceinline__ void load_site_buf(K keep, const S *__restrict__ src,
   for (int b = 0; b < 3; ++b) {
     const int zs = L::D == 3 ? wrap_sub(z, b - 1, nz) : z;
     rs[b] = make_rsrc(src + (int64_t)zs * plane, pbytes);
+  }
+  if constexpr (FLAT) {
+    const PlaneOffsets<L, S> o(nx, ny, x, y);
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i) {
+      const uint32_t v = o.site(L::cx[i], L::cy[i]);
+      if (NT_C0 && L::cx[i] == 0)
+        keep(i, buf_load<S, true>(rs[L::cz[i] + 1], v, o.population(i)));
+      else
+        keep(i, buf_load<S, false>(rs[L::cz[i] + 1], v, o.population(i)));
+    }
+    return;
   }
   const uint32_t xs[3] = {(uint32_t)(x == nx - 1 ? 0 : x + 1) * B, (uint32_t)x * B,
                           (uint32_t)(x == 0 ? nx - 1 : x - 1) * B};
@@ -607,7 +640,7 @@ __device__ __forceinline__ void load_site_buf(K keep, const S *__restrict__ src,
   }
 }
 
-template <class L, typename S, typename R, bool NT>
+template <class L, typename S, typename R, bool NT, bool FLAT>
 __device__ __forceinline__ void store_site_buf(const R *d, S *__restrict__ dst,
                                                const float *iscale, int nx, int ny, int x,
                                                int y, int z) {
@@ -616,6 +649,14 @@ __device__ __forceinline__ void store_site_buf(const R *d, S *__restrict__ dst,
   const int64_t plane = (int64_t)ny * L::Q * nx;
   const __amdgpu_buffer_rsrc_t r = make_rsrc(dst + (int64_t)z * plane, (uint32_t)(plane * B));
   const uint32_t rowb = (uint32_t)nx * B;
+  if constexpr (FLAT) {
+    const uint32_t v = (uint32_t)y * (uint32_t)L::Q * rowb + (uint32_t)x * B;
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i)
+      buf_store<S, NT>(ST::to_bits(d[i], iscale[weight_class<L>(i)]), r, v,
+                       (uint32_t)pop_slot<L>(i) * rowb);
+    return;
+  }
   const uint32_t blk = (uint32_t)y * (uint32_t)L::Q;
 #pragma unroll
   for (int i = 0; i < L::Q; ++i)
@@ -625,12 +666,42 @@ __device__ __forceinline__ void store_site_buf(const R *d, S *__restrict__ dst,
 
 struct TileXY {
   int x, y, z;
+  bool inside;
 };
 
-__device__ __forceinline__ TileXY tile_coords(int tile, int nxb, int ny, int bx) {
-  const int xb = tile % nxb;
-  const int row = tile / nxb;
-  return TileXY{xb * bx + (int)threadIdx.x, row % ny, row / ny};
+// Workgroups are handed to the XCDs round-robin by id and every XCD has its
+// own L2.  Map workgroup b to a tile so that runs of CHUNK adjacent tiles go
+// to one XCD (run c to XCD c mod kXcds): two tiles that split a lattice row,
+// or that pull from each other's rows, then mostly meet in the same L2, which
+// merges the two parts of a shared cache line before it goes to HBM; the
+// runs rotate over the XCDs, so tiles of different cost (D2Q9 and D3Q27
+// replicas of an ensemble) spread evenly.  A bijection on [0, n): the last
+// n mod (kXcds CHUNK) tiles keep their own ids.
+template <int CHUNK>
+__device__ __forceinline__ int xcd_tile(int b, int n) {
+  constexpr int G = kXcds * CHUNK;
+  if (b >= n / G * G) return b;
+  const int j = b % kXcds, k = b / kXcds;
+  return ((k / CHUNK) * kXcds + j) * CHUNK + k % CHUNK;
+}
+
+// The site of this thread in a tile: of a row of the lattice, or (FLAT) of
+// the sites of a z plane in a row.  There a lane's row and column follow from
+// those of the tile's first site by one product: t (m nx - 2^32) <= t nx <
+// 2^32 for m = 2^32 / nx + 1 and t < nx + 256.
+template <bool FLAT, class P>
+__device__ __forceinline__ TileXY tile_coords(int tile, const P &p, int bx) {
+  const int xb = tile % p.nxb;
+  const int row = tile / p.nxb;
+  if constexpr (FLAT) {
+    const int first = xb * bx;
+    const int y0 = first / p.nx;
+    const int t = first - y0 * p.nx + (int)threadIdx.x;
+    const int dy = (int)__umulhi((uint32_t)t, p.flat);
+    return TileXY{t - dy * p.nx, y0 + dy, row, y0 + dy < p.ny};
+  }
+  const int x = xb * bx + (int)threadIdx.x;
+  return TileXY{x, row % p.ny, row / p.ny, x < p.nx};
 }
 
 // The statistics of a workgroup's tile go to its row of the partial sums, or
@@ -656,7 +727,9 @@ __device__ __forceinline__ void store_tile_stats(const A &acc, const P &p, doubl
 // BUF: buffer-addressed population accesses (every z plane of the buffer
 // below 4 GiB); otherwise 64-bit addresses.
 // FIRST: normals before populations (kDrawFirst).
-template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool BUF, bool FIRST>
+// FLAT: tiles of a z plane's sites (BUF only).
+template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool BUF, bool FIRST,
+          bool FLAT>
 __global__ __launch_bounds__(kMaxBlock) void k_step(
     const S *__restrict__ src, S *__restrict__ dst, const StepParams<R> p,
     const int64_t *__restrict__ step_ptr, int step_off, double *__restrict__ partials) {
@@ -667,12 +740,12 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(
   A acc{};
 
   for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
-    const TileXY c = tile_coords(tile, p.nxb, ny, BX);
-    if (c.x < nx) {
+    const TileXY c = tile_coords<FLAT>(FLAT ? xcd_tile<kFlatXcdChunk>(tile, p.ntiles) : tile, p, BX);
+    if (c.inside) {
       Pulled<L, S, R, FIRST> f{p.scale};
       auto keep = [&](int i, typename Store<S, R>::bits_t b) { f.keep(i, b); };
       if constexpr (BUF)
-        load_site_buf<L, S, NT>(keep, src, nx, ny, p.nz, c.x, c.y, c.z);
+        load_site_buf<L, S, NT, FLAT>(keep, src, nx, ny, p.nz, c.x, c.y, c.z);
       else
         load_site<L, S, NT>(keep, src, nx, ny, p.nz, c.x, c.y, c.z);
       const int64_t row = (int64_t)c.y + (int64_t)ny * c.z;
@@ -681,7 +754,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(
       R *d = f.d;
       collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, acc);
       if constexpr (BUF)
-        store_site_buf<L, S, R, NT>(d, dst, p.iscale, nx, ny, c.x, c.y, c.z);
+        store_site_buf<L, S, R, NT, FLAT>(d, dst, p.iscale, nx, ny, c.x, c.y, c.z);
       else
         store_site<L, S, R, NT>(d, dst, p.iscale, nx, c.x, row);
     }
@@ -699,14 +772,20 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(
 // NT (population rows of whole cache lines): non-temporal accesses where a
 // tile covers whole rows, every access of the even step and the c_x = 0
 // accesses of the odd step.
-template <class L, typename S, bool NT, bool ODD, class K>
+template <class L, typename S, bool NT, bool ODD, bool FLAT, class K>
 __device__ __forceinline__ void load_site_aa(K keep, const S *buf, int nx, int ny, int nz, int x,
                                              int y, int z) {
   constexpr uint32_t B = sizeof(S);
   const int64_t plane = (int64_t)ny * L::Q * nx;
   const uint32_t pbytes = (uint32_t)(plane * B);
   const uint32_t rowb = (uint32_t)nx * B;
-  if constexpr (!ODD) {
+  if constexpr (!ODD && FLAT) {
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(buf + (int64_t)z * plane, pbytes);
+    const uint32_t v = (uint32_t)y * (uint32_t)L::Q * rowb + (uint32_t)x * B;
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i)
+      keep(i, buf_load<S, NT>(r, v, (uint32_t)pop_slot<L>(i) * rowb));
+  } else if constexpr (!ODD) {
     const __amdgpu_buffer_rsrc_t r = make_rsrc(buf + (int64_t)z * plane, pbytes);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i)
@@ -717,6 +796,18 @@ __device__ __forceinline__ void load_site_aa(K keep, const S *buf, int nx, int n
     for (int b = 0; b < 3; ++b) {
       const int zs = L::D == 3 ? wrap_sub(z, b - 1, nz) : z;
       rs[b] = make_rsrc(buf + (int64_t)zs * plane, pbytes);
+    }
+    if constexpr (FLAT) {
+      const PlaneOffsets<L, S> o(nx, ny, x, y);
+#pragma unroll
+      for (int i = 0; i < L::Q; ++i) {
+        const uint32_t v = o.site(L::cx[i], L::cy[i]), soff = o.population(opposite<L>(i));
+        if (NT && L::cx[i] == 0)
+          keep(i, buf_load<S, true>(rs[L::cz[i] + 1], v, soff));
+        else
+          keep(i, buf_load<S, false>(rs[L::cz[i] + 1], v, soff));
+      }
+      return;
     }
     const uint32_t xs[3] = {(uint32_t)(x == nx - 1 ? 0 : x + 1) * B, (uint32_t)x * B,
                             (uint32_t)(x == 0 ? nx - 1 : x - 1) * B};
@@ -735,7 +826,7 @@ __device__ __forceinline__ void load_site_aa(K keep, const S *buf, int nx, int n
   }
 }
 
-template <class L, typename S, typename R, bool NT, bool ODD>
+template <class L, typename S, typename R, bool NT, bool ODD, bool FLAT>
 __device__ __forceinline__ void store_site_aa(const R *d, S *buf, const float *iscale, int nx,
                                               int ny, int nz, int x, int y, int z) {
   using ST = Store<S, R>;
@@ -743,7 +834,14 @@ __device__ __forceinline__ void store_site_aa(const R *d, S *buf, const float *i
   const int64_t plane = (int64_t)ny * L::Q * nx;
   const uint32_t pbytes = (uint32_t)(plane * B);
   const uint32_t rowb = (uint32_t)nx * B;
-  if constexpr (!ODD) {
+  if constexpr (!ODD && FLAT) {
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(buf + (int64_t)z * plane, pbytes);
+    const uint32_t v = (uint32_t)y * (uint32_t)L::Q * rowb + (uint32_t)x * B;
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i)
+      buf_store<S, NT>(ST::to_bits(d[i], iscale[weight_class<L>(i)]), r, v,
+                       (uint32_t)pop_slot<L>(opposite<L>(i)) * rowb);
+  } else if constexpr (!ODD) {
     const __amdgpu_buffer_rsrc_t r = make_rsrc(buf + (int64_t)z * plane, pbytes);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i)
@@ -756,6 +854,19 @@ __device__ __forceinline__ void store_site_aa(const R *d, S *buf, const float *i
     for (int b = 0; b < 3; ++b) {
       const int zd = L::D == 3 ? wrap_sub(z, 1 - b, nz) : z;
       rd[b] = make_rsrc(buf + (int64_t)zd * plane, pbytes);
+    }
+    if constexpr (FLAT) {
+      const PlaneOffsets<L, S> o(nx, ny, x, y);
+#pragma unroll
+      for (int i = 0; i < L::Q; ++i) {
+        const uint32_t to = o.site(-L::cx[i], -L::cy[i]), soff = o.population(i);
+        const auto bits = ST::to_bits(d[i], iscale[weight_class<L>(i)]);
+        if (NT && L::cx[i] == 0)
+          buf_store<S, true>(bits, rd[L::cz[i] + 1], to, soff);
+        else
+          buf_store<S, false>(bits, rd[L::cz[i] + 1], to, soff);
+      }
+      return;
     }
     const uint32_t xd[3] = {(uint32_t)(x == 0 ? nx - 1 : x - 1) * B, (uint32_t)x * B,
                             (uint32_t)(x == nx - 1 ? 0 : x + 1) * B};
@@ -779,7 +890,7 @@ __device__ __forceinline__ void store_site_aa(const R *d, S *buf, const float *i
 // half of a pair of steps); tiles, statistics and ONE as in k_step.  Every
 // element is read and then written by the same thread only, and each store
 // depends on every load of its site through the collision.
-template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool ODD>
+template <class L, typename S, typename R, bool GENERAL, bool NT, bool ONE, bool ODD, bool FLAT>
 __global__ __launch_bounds__(kMaxBlock) void k_step_aa(
     S *buf, const StepParams<R> p, const int64_t *__restrict__ step_ptr, int step_off,
     double *__restrict__ partials) {
@@ -790,18 +901,18 @@ __global__ __launch_bounds__(kMaxBlock) void k_step_aa(
   A acc{};
 
   for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
-    const TileXY c = tile_coords(tile, p.nxb, ny, BX);
-    if (c.x < nx) {
+    const TileXY c = tile_coords<FLAT>(FLAT ? xcd_tile<kFlatXcdChunk>(tile, p.ntiles) : tile, p, BX);
+    if (c.inside) {
       // (in place, D3Q27 draws late too: 256^3 FP32 644 against 651 us)
       Pulled<L, S, R, kDrawFirst<L, S> && L::Q != 27> f{p.scale};
       auto keep = [&](int i, typename Store<S, R>::bits_t b) { f.keep(i, b); };
-      load_site_aa<L, S, NT, ODD>(keep, buf, nx, ny, p.nz, c.x, c.y, c.z);
+      load_site_aa<L, S, NT, ODD, FLAT>(keep, buf, nx, ny, p.nz, c.x, c.y, c.z);
       const int64_t row = (int64_t)c.y + (int64_t)ny * c.z;
       const int site = (int)(c.x + nx * row);
       const auto normals = f.normals(p, (uint32_t)site, step);
       R *d = f.d;
       collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, acc);
-      store_site_aa<L, S, R, NT, ODD>(d, buf, p.iscale, nx, ny, p.nz, c.x, c.y, c.z);
+      store_site_aa<L, S, R, NT, ODD, FLAT>(d, buf, p.iscale, nx, ny, p.nz, c.x, c.y, c.z);
     }
     if constexpr (ONE) break;
   }
@@ -818,7 +929,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_step_aa(
 namespace step_launch {
 
 // MODE: a StreamMode (the in-place modes only with BUF)
-template <class L, typename S, typename R, bool G, bool NT, bool BUF, int MODE>
+template <class L, typename S, typename R, bool G, bool NT, bool BUF, int MODE, bool FLAT>
 hipError_t shape(const StepParams<R> &p, const void *src, void *dst,
                  const int64_t *step_ptr, int step_off, double *partials, int grid,
                  int block, hipStream_t stream) {
@@ -826,18 +937,18 @@ hipError_t shape(const StepParams<R> &p, const void *src, void *dst,
     constexpr bool ONE = decltype(one)::value;
     if constexpr (MODE == kStreamPull && L::Q == 27 && sizeof(S) == 4) {
       if ((int64_t)p.nx * p.ny * p.nz > kDrawFirstSites) {
-        hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF, false>), dim3(nblocks), dim3(block),
+        hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF, false, FLAT>), dim3(nblocks), dim3(block),
                            lds, stream, static_cast<const S *>(src), static_cast<S *>(dst), p,
                            step_ptr, step_off, partials);
         return hipGetLastError();
       }
     }
     if constexpr (MODE == kStreamPull)
-      hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF, kDrawFirst<L, S>>), dim3(nblocks),
+      hipLaunchKernelGGL((k_step<L, S, R, G, NT, ONE, BUF, kDrawFirst<L, S>, FLAT>), dim3(nblocks),
                          dim3(block), lds, stream, static_cast<const S *>(src),
                          static_cast<S *>(dst), p, step_ptr, step_off, partials);
     else
-      hipLaunchKernelGGL((k_step_aa<L, S, R, G, NT, ONE, MODE == kStreamAAOdd>), dim3(nblocks),
+      hipLaunchKernelGGL((k_step_aa<L, S, R, G, NT, ONE, MODE == kStreamAAOdd, FLAT>), dim3(nblocks),
                          dim3(block), lds, stream, static_cast<S *>(dst), p, step_ptr, step_off,
                          partials);
     return hipGetLastError();
@@ -863,20 +974,28 @@ hipError_t one(int mode, const void *params, const void *src, void *dst,
   // population buffer spans less than 4 GiB (always so for in-place
   // streaming, which the library accepts only then)
   const bool buf = (int64_t)p.ny * L::Q * p.nx * (int64_t)sizeof(S) < ((int64_t)1 << 32);
-  if constexpr (IN_PLACE) {
+  if (p.flat && (!buf || L::Q == 9)) return hipErrorInvalidValue;
+  auto buffered = [&](auto flat) {
+    constexpr bool FLAT = decltype(flat)::value;
+    if constexpr (!IN_PLACE)
+      return shape<L, S, R, G, NT, true, kStreamPull, FLAT>(p, src, dst, step_ptr, step_off,
+                                                            partials, grid, block, stream);
+    else if (mode == kStreamAAEven)
+      return shape<L, S, R, G, NT, true, kStreamAAEven, FLAT>(p, src, dst, step_ptr, step_off,
+                                                              partials, grid, block, stream);
+    else
+      return shape<L, S, R, G, NT, true, kStreamAAOdd, FLAT>(p, src, dst, step_ptr, step_off,
+                                                             partials, grid, block, stream);
+  };
+  if constexpr (IN_PLACE)
     if (!buf || src != dst) return hipErrorInvalidValue;
-    return mode == kStreamAAEven
-               ? shape<L, S, R, G, NT, true, kStreamAAEven>(p, src, dst, step_ptr, step_off,
-                                                            partials, grid, block, stream)
-               : shape<L, S, R, G, NT, true, kStreamAAOdd>(p, src, dst, step_ptr, step_off,
-                                                           partials, grid, block, stream);
-  } else {
-    if (buf)
-      return shape<L, S, R, G, NT, true, kStreamPull>(p, src, dst, step_ptr, step_off, partials,
-                                                      grid, block, stream);
-    return shape<L, S, R, G, NT, false, kStreamPull>(p, src, dst, step_ptr, step_off, partials,
-                                                     grid, block, stream);
-  }
+  if constexpr (L::Q != 9)
+    if (p.flat) return buffered(std::true_type{});
+  if constexpr (!IN_PLACE)
+    if (!buf)
+      return shape<L, S, R, G, NT, false, kStreamPull, false>(p, src, dst, step_ptr, step_off,
+                                                              partials, grid, block, stream);
+  return buffered(std::false_type{});
 }
 
 template <bool IN_PLACE, class L, typename S, typename R>
