@@ -807,40 +807,32 @@ struct FetchRing {
   }
 };
 
-// chunks 0 .. n - 1 in order: copies enqueued by this thread, emptied by the
-// others; chunk c uses slot c mod kFetchSlots once chunk c - kFetchSlots is out
-hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s, FetchRing &ring,
-                        int device) {
+// chunks 0 .. n - 1 in order: copies enqueued and waited for by this thread
+// (the only one that calls the runtime), emptied by the others; chunk c uses
+// slot c mod kFetchSlots once chunk c - kFetchSlots is out
+hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s, FetchRing &ring) {
   const int64_t n = (int64_t)((bytes + kFetchChunk - 1) / kFetchChunk);
   std::mutex mu;
   std::condition_variable cv;
-  int64_t issued = 0, taken = 0;
-  std::vector<char> out(n, 0);
-  hipError_t err = hipSuccess;  // all guarded by mu
+  int64_t landed = 0, taken = 0;
+  bool stop = false;
+  std::vector<char> out(n, 0);  // all guarded by mu
   auto size_of = [&](int64_t c) {
     const size_t at = (size_t)c * kFetchChunk;
     return bytes - at < kFetchChunk ? bytes - at : kFetchChunk;
   };
   auto work = [&]() {
-    hipError_t e = hipSetDevice(device);
-    for (;;) {
-      std::unique_lock<std::mutex> lk(mu);
-      if (e != hipSuccess && err == hipSuccess) err = e;
-      if (err != hipSuccess || taken == n) break;
+    std::unique_lock<std::mutex> lk(mu);
+    while (!stop && taken < n) {
       const int64_t c = taken++;
-      cv.wait(lk, [&] { return issued > c || err != hipSuccess; });
-      if (err != hipSuccess) break;
+      cv.wait(lk, [&] { return landed > c || stop; });
+      if (landed <= c) break;
       lk.unlock();
-      e = hipEventSynchronize(ring.ready[c % kFetchSlots]);
-      if (e == hipSuccess)
-        memcpy(dst + (size_t)c * kFetchChunk, ring.pin + (size_t)(c % kFetchSlots) * kFetchChunk, size_of(c));
+      memcpy(dst + (size_t)c * kFetchChunk, ring.pin + (size_t)(c % kFetchSlots) * kFetchChunk, size_of(c));
       lk.lock();
       out[c] = 1;
-      if (e != hipSuccess && err == hipSuccess) err = e;
-      lk.unlock();
       cv.notify_all();
     }
-    cv.notify_all();
   };
   std::vector<std::thread> threads;
   threads.reserve(kFetchThreads);
@@ -850,27 +842,34 @@ hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s,
     // fewer threads, or none: the copies below need at least one
   }
   if (threads.empty()) return hipErrorOutOfMemory;
-  for (int64_t c = 0; c < n; ++c) {
-    {
-      std::unique_lock<std::mutex> lk(mu);
-      cv.wait(lk, [&] { return err != hipSuccess || c < kFetchSlots || out[c - kFetchSlots]; });
-      if (err != hipSuccess) break;
+  hipError_t e = hipSuccess;
+  int64_t issued = 0;
+  for (int64_t c = 0; c < n && e == hipSuccess; ++c) {
+    for (; issued < n && issued < c + kFetchSlots && e == hipSuccess; ++issued) {
+      if (issued >= kFetchSlots) {
+        // the slot's last chunk is out, or waited for where chunk c needs it
+        std::unique_lock<std::mutex> lk(mu);
+        if (issued == c) cv.wait(lk, [&] { return out[issued - kFetchSlots] != 0; });
+        if (!out[issued - kFetchSlots]) break;
+      }
+      const int slot = (int)(issued % kFetchSlots);
+      e = hipMemcpyAsync(ring.pin + (size_t)slot * kFetchChunk, src + (size_t)issued * kFetchChunk,
+                         size_of(issued), hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipEventRecord(ring.ready[slot], s);
     }
-    const int slot = (int)(c % kFetchSlots);
-    hipError_t e = hipMemcpyAsync(ring.pin + (size_t)slot * kFetchChunk, src + (size_t)c * kFetchChunk, size_of(c),
-                                  hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipEventRecord(ring.ready[slot], s);
+    if (e == hipSuccess) e = hipEventSynchronize(ring.ready[c % kFetchSlots]);
     {
       std::lock_guard<std::mutex> lk(mu);
-      if (e != hipSuccess) err = e;
-      issued = c + 1;
+      if (e == hipSuccess)
+        landed = c + 1;
+      else
+        stop = true;
     }
     cv.notify_all();
-    if (e != hipSuccess) break;
   }
   for (auto &t : threads) t.join();
   (void)hipStreamSynchronize(s);  // no copy into the ring outlives it
-  return err;
+  return e;
 }
 
 // `bytes` from device memory at src to dst, after the work already on s;
@@ -878,10 +877,9 @@ hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s,
 hipError_t fetch(void *dst, const void *src, size_t bytes, hipStream_t s) {
   if (bytes >= 2 * kFetchChunk) {
     FetchRing ring;
-    int device = 0;
-    if (ring.init() && hipGetDevice(&device) == hipSuccess) {
+    if (ring.init()) {
       try {
-        const hipError_t e = fetch_chunks((char *)dst, (const char *)src, bytes, s, ring, device);
+        const hipError_t e = fetch_chunks((char *)dst, (const char *)src, bytes, s, ring);
         if (e == hipSuccess) return e;
         (void)hipGetLastError();
       } catch (const std::bad_alloc &) {
