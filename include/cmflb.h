@@ -235,15 +235,16 @@ typedef struct {
 int cmf_get_launch(cmf_lattice *lat, cmf_launch *out);
 
 /* Set the launch shape: block in {64, 128, 192, 256}, grid >= 1 (capped at
- * the number of tiles).  Results do not depend on it (the noise is keyed by
+ * the number of tiles: of `block` sites of a row, or, on 3-D boxes whose rows
+ * would leave lanes idle, of `block` consecutive sites of a z plane).  Results do not depend on it (the noise is keyed by
  * the site), only the speed and the summation order of the statistics.
  * From then on every step is one launch of that shape, also for the small
  * D2Q9 boxes that otherwise take several steps per launch, until
  * cmf_autotune.  Synchronises; drops captured graphs. */
 int cmf_set_launch(cmf_lattice *lat, int32_t block, int32_t grid);
 
-/* Autotuner: time every candidate launch shape (block 64..256 up to the
- * row length; grid 1, 2, 4, 8, 16 and 32 x the compute-unit count, and one
+/* Autotuner: time every candidate launch shape (block 64..256, up to the
+ * row length where tiles are parts of a row; grid 1, 2, 4, 8, 16 and 32 x the compute-unit count, and one
  * tile per workgroup, which is the only grid of the small D2Q9 boxes that
  * take several steps per launch) with `steps_per_trial` real steps each (after one
  * untimed step; a step = fused kernel + statistics finalize), then restore the state, step counter and statistics ring
@@ -338,8 +339,13 @@ int cmf_get_macro(cmf_lattice *lat, double *rho, double *u);
  *   b = 0 counts x < -xmax and non-finite x, b = 1..nbins split [-xmax, xmax)
  *   into equal bins, b = nbins + 1 counts x >= xmax (z entries are zero on
  *   D2Q9).  moments (12 doubles) or counts (3 (nbins + 2) int64) may be NULL.
- * Three device passes (means, central moments, histogram), fixed-order FP64
- * sums and integer counts; allocates temporary device buffers.
+ * Three device passes (means, central moments, histogram) and one wait,
+ * fixed-order FP64 sums and integer counts.  The first call allocates a
+ * workspace of about 300 KB that stays with the lattice; the velocities are
+ * kept between the passes in the population buffer that the next step
+ * overwrites, where the lattice owns two that hold them, and computed again
+ * from the populations otherwise (in place, caller-owned buffers, 16-bit
+ * storage where they do not fit).
  * Errors: CMF_EINVAL (nbins outside [1, 4096] or xmax <= 0 with counts).
  * Synchronous. */
 int cmf_velocity_pdf(cmf_lattice *lat, int32_t nbins, double xmax, double *moments,
@@ -369,7 +375,8 @@ int cmf_philox_words(const uint32_t *ctr, int64_t n, uint32_t key0,
  * |k| = 2 pi sqrt((m_x/n_x)^2 + ...) are reduced in a fixed order. */
 
 /* Allocate (first call) and zero the accumulators, with `nbins` shells of
- * equal width on [0, pi sqrt(d)] (1 <= nbins <= 1024).  Synchronous. */
+ * equal width on [0, pi sqrt(d)] (1 <= nbins <= 1024).  The modes are sorted
+ * into shells on the device.  Synchronous. */
 int cmf_sk_reset(cmf_lattice *lat, int32_t nbins);
 
 /* Add one sample: the current pre-collision state.  Asynchronous on the

@@ -523,7 +523,7 @@ bool lookup_tuned(const cmf_lattice *L, int *block, int *grid) {
 // Workgroup size of an untuned lattice: the one whose tiles cover the box with
 // the fewest lanes, weighted by what a lane costs in a workgroup of that size
 // (the start of a workgroup and its statistics are shared by its lanes).  One
-// tile per workgroup, D3Q27, us per step at 64 / 128 / 192 / 256 threads: nx =
+// tile per workgroup, D3Q27 in tiles of a row, us per step at 64 / 128 / 192 / 256 threads: nx =
 // 300 FP32 110 / 101 / 104 / 114, FP64 207 / 218 / 222 / 262; nx = 200 FP32 160 /
 // 159 / 175 / 119, FP64 317 / 314 / 412 / 309; nx = 160 FP32 147 / 162 / 138; nx =
 // 100 FP32 58 / 48.

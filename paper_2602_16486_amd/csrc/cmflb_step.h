@@ -386,7 +386,7 @@ __device__ __forceinline__ void collide_site(R *d, const P &p, const NM &normals
 // draw is a block of its own behind a scalar branch, across which the compiler
 // moves neither loads nor their waits: placed first, one wave's noise covers
 // its own loads, for the registers that hold the drawn parts meanwhile.  FP32
-// steps gain (us, one machine: D3Q27 50^3 16.5 -> 15.7, 128^3 91 -> 87, D3Q19 256^3
+// steps gain (us, one machine: D3Q27 50^3 in tiles of a row 16.5 -> 15.7, 128^3 91 -> 87, D3Q19 256^3
 // 431 -> 414, D2Q9 4096^2 223 -> 216, the 320-replica ensemble 955 -> 944), but for
 // D3Q27 lattices well beyond the last-level cache, which wait for HBM with
 // either order and keep five waves per SIMD instead of four (256^3 612 against
