@@ -81,9 +81,13 @@ __global__ __launch_bounds__(1024) void k_step_fused(
     }
   };
 
-  for (int j = 0; j < nsteps; ++j) {
-    if (partials && j > 0) reduce(j - 1);
-    const int h = nsteps - 1 - j;  // sites computed beyond the tile
+  // step j: the first from HBM, the last to HBM, the others from LDS to LDS
+  // (`first` and `last` a constant's type where each kind has its own code)
+  auto step = [&](auto first, auto last, int j) {
+    constexpr bool LAST = std::is_same<decltype(last), std::true_type>::value;
+    constexpr bool INNER = std::is_same<decltype(last), std::false_type>::value;
+    if (partials && !first) reduce(j - 1);
+    const int h = LAST ? 0 : nsteps - 1 - j;  // sites computed beyond the tile
     const int rw = w + 2 * h, area = rw * (hgt + 2 * h);
     // i / rw by a multiplication, exact for i < 4096 and rw <= 256 (i (m rw
     // - 2^20) <= i rw < 2^20 with m = 2^20 / rw + 1)
@@ -96,7 +100,7 @@ __global__ __launch_bounds__(1024) void k_step_fused(
       const int lidx = (ry + j) * RX + rx + j;  // in the first step's region
       // (FP64 draws when it collides: 64^2 without noise 1.51 against 1.58 us)
       Pulled<L, S, R, sizeof(S) == 4> f{p.scale};
-      if (j == 0) {
+      if (first) {
         const uint32_t xs[3] = {(uint32_t)wrap_sub(gx, -1, nx) * B, (uint32_t)gx * B,
                                 (uint32_t)wrap_sub(gx, 1, nx) * B};
         const uint32_t ys[3] = {(uint32_t)wrap_sub(gy, -1, ny) * Q * rowb, (uint32_t)gy * Q * rowb,
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_step_fused(
       R *d = f.d;
       SiteStats<R> st;
       collide_site<L, R, GENERAL, sizeof(S) == 2>(d, p, normals, st);
-      if (h > 0) {
+      if (INNER || h > 0) {
         auto *to = &lds.pop[j & 1][0][lidx];
 #pragma unroll
         for (int q = 0; q < Q; ++q)
@@ -136,6 +140,16 @@ __global__ __launch_bounds__(1024) void k_step_fused(
       }
     }
     __syncthreads();
+  };
+  // The first and last step in code of their own take 7-10 % less time (us per
+  // step, 64^2 FP32 1.87 -> 1.71, 200^2 2.77 -> 2.59, 250 x 255 FP16 3.41 -> 3.14);
+  // FP64 then spills scalar registers (64^2 1.49 -> 1.57) and keeps one loop.
+  if (sizeof(R) == 8 || nsteps == 1) {
+    for (int j = 0; j < nsteps; ++j) step(j == 0, j, j);
+  } else {
+    step(std::true_type{}, std::false_type{}, 0);
+    for (int j = 1; j < nsteps - 1; ++j) step(std::false_type{}, std::false_type{}, j);
+    step(std::false_type{}, std::true_type{}, nsteps - 1);
   }
   if (partials) reduce(nsteps - 1);
 }
