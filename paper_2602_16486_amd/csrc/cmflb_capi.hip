@@ -313,6 +313,39 @@ int capture_forked(hipStream_t s, ForkedRun &F, bool stats, int K, int64_t *step
   return CMF_OK;
 }
 
+// The pinned chunks of large copies to the host (see fetch) of one lattice or
+// ensemble, from its first such copy until its end.
+constexpr size_t kFetchChunk = (size_t)4 << 20;
+constexpr int kFetchSlots = 6, kFetchThreads = 4;
+
+struct FetchRing {
+  char *pin = nullptr;
+  hipEvent_t ready[kFetchSlots] = {};
+  FetchRing() = default;
+  FetchRing(const FetchRing &) = delete;
+  FetchRing &operator=(const FetchRing &) = delete;
+  ~FetchRing() { release(); }
+  void release() {
+    for (auto &e : ready) {
+      if (e) (void)hipEventDestroy(e);
+      e = nullptr;
+    }
+    if (pin) (void)hipHostFree(pin);
+    pin = nullptr;
+  }
+  bool init() {
+    if (pin) return true;
+    bool ok = true;
+    for (auto &e : ready) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipHostMalloc((void **)&pin, kFetchSlots * kFetchChunk, hipHostMallocDefault) == hipSuccess;
+    if (!ok) {
+      (void)hipGetLastError();
+      release();
+    }
+    return ok;
+  }
+};
+
 }  // namespace
 
 struct cmf_lattice {
@@ -355,6 +388,7 @@ struct cmf_lattice {
   ConvParams cp;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   ForkedRun forked;
+  FetchRing ring;
   char *vel_ws = nullptr;  // velocity statistics: VelState, counts, block sums
   // structure factor
   int sk_nbins = 0;
@@ -553,7 +587,9 @@ int default_block(const cmf_desc &d) {
 // 6.43).  Beyond two per CU the sites computed twice outweigh the launches
 // saved (400 x 300, 475 tiles of 16: 4.94 against 8.50; 700 x 500, 1408: 13.2
 // against 11.7; 512^2, 1024: FP32 9.2 against 10.3, FP16 9.5 against 8.1, FP64
-// 20.6 against 15.2).  A launch shape that was asked for keeps single steps
+// 20.6 against 15.2; all before the first and last step of a launch had code
+// of their own, which takes 7-10 % off FP32 and 16-bit launches).  A launch
+// shape that was asked for keeps single steps
 // in that shape.  Boxes of this size keep their statistics in cell order
 // whether or not they can take several steps (in-place streaming and edges
 // up to kFusedSteps cannot).
@@ -786,31 +822,14 @@ int run_fused(cmf_lattice *L, int n) {
 // against 56 GB/s of the link to pinned memory.  Large arrays therefore go
 // through a ring of pinned chunks that kFetchThreads threads empty into the
 // caller's array, whose page faults they share (57 MB into a new numpy array 5.8 ->
-// 2.2 ms, 453 MB 45 -> 13; pinning the ring, for the length of the call, takes
-// 0.3).
-constexpr size_t kFetchChunk = (size_t)4 << 20;
-constexpr int kFetchSlots = 6, kFetchThreads = 4;
-
-struct FetchRing {
-  char *pin = nullptr;
-  hipEvent_t ready[kFetchSlots] = {};
-  ~FetchRing() {
-    for (auto &e : ready)
-      if (e) (void)hipEventDestroy(e);
-    if (pin) (void)hipHostFree(pin);
-  }
-  bool init() {
-    bool ok = hipHostMalloc((void **)&pin, kFetchSlots * kFetchChunk, hipHostMallocDefault) == hipSuccess;
-    for (auto &e : ready) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-    return ok;
-  }
-};
+// 2.1 ms, 453 MB 45 -> 12).  The ring stays with the lattice: pinned for each
+// call it took 0.3 ms of it, and 4 ms once three ensembles were asked in turn
+// (54 MB 5.9 against 2.2 ms).
 
 // chunks 0 .. n - 1 in order: copies enqueued and waited for by this thread
 // (the only one that calls the runtime), emptied by the others; chunk c uses
 // slot c mod kFetchSlots once chunk c - kFetchSlots is out
-hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s, FetchRing &ring) {
+hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, FetchRing &ring) {
   const int64_t n = (int64_t)((bytes + kFetchChunk - 1) / kFetchChunk);
   std::mutex mu;
   std::condition_variable cv;
@@ -854,8 +873,8 @@ hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s,
       }
       const int slot = (int)(issued % kFetchSlots);
       e = hipMemcpyAsync(ring.pin + (size_t)slot * kFetchChunk, src + (size_t)issued * kFetchChunk,
-                         size_of(issued), hipMemcpyDeviceToHost, s);
-      if (e == hipSuccess) e = hipEventRecord(ring.ready[slot], s);
+                         size_of(issued), hipMemcpyDeviceToHost, nullptr);
+      if (e == hipSuccess) e = hipEventRecord(ring.ready[slot], nullptr);
     }
     if (e == hipSuccess) e = hipEventSynchronize(ring.ready[c % kFetchSlots]);
     {
@@ -868,27 +887,26 @@ hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, hipStream_t s,
     cv.notify_all();
   }
   for (auto &t : threads) t.join();
-  (void)hipStreamSynchronize(s);  // no copy into the ring outlives it
+  (void)hipStreamSynchronize(nullptr);  // no copy into the ring outlives it
   return e;
 }
 
 // `bytes` from device memory at src to dst, after the work already on s;
-// returns when they are there.
-hipError_t fetch(void *dst, const void *src, size_t bytes, hipStream_t s) {
+// returns when they are there (through the default stream, as hipMemcpy).
+hipError_t fetch(FetchRing &ring, void *dst, const void *src, size_t bytes, hipStream_t s) {
+  const hipError_t w = hipStreamSynchronize(s);
+  if (w != hipSuccess) return w;
   if (bytes >= 2 * kFetchChunk) {
-    FetchRing ring;
     if (ring.init()) {
       try {
-        const hipError_t e = fetch_chunks((char *)dst, (const char *)src, bytes, s, ring);
+        const hipError_t e = fetch_chunks((char *)dst, (const char *)src, bytes, ring);
         if (e == hipSuccess) return e;
         (void)hipGetLastError();
       } catch (const std::bad_alloc &) {
       }
     }
   }
-  const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
-  const hipError_t w = hipStreamSynchronize(s);
-  return e != hipSuccess ? e : w;
+  return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
 }
 
 // Rows of steps [first, step), at most cap of them, from a series ring on the
@@ -1258,7 +1276,7 @@ int cmf_get_populations(cmf_lattice *L, double *f) {
   if (hipMalloc((void **)&df, bytes) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_get_state(L->q, L->storage, conv(L), L->buf[L->parity], df, L->stream);
-  if (e == hipSuccess) e = fetch(f, df, bytes, L->stream);
+  if (e == hipSuccess) e = fetch(L->ring, f, df, bytes, L->stream);
   (void)hipFree(df);
   if (e != hipSuccess) return fail(CMF_EHIP, "get_populations failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -1652,8 +1670,8 @@ int cmf_get_macro(cmf_lattice *L, double *rho, double *u) {
   if (hipMalloc((void **)&d, bytes) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_macro(L->q, L->storage, conv(L), L->buf[L->parity], d, d + L->N, L->stream);
-  if (e == hipSuccess && rho) e = fetch(rho, d, sizeof(double) * L->N, L->stream);
-  if (e == hipSuccess && u) e = fetch(u, d + L->N, sizeof(double) * 3 * L->N, L->stream);
+  if (e == hipSuccess && rho) e = fetch(L->ring, rho, d, sizeof(double) * L->N, L->stream);
+  if (e == hipSuccess && u) e = fetch(L->ring, u, d + L->N, sizeof(double) * 3 * L->N, L->stream);
   (void)hipFree(d);
   if (e != hipSuccess) return fail(CMF_EHIP, "get_macro failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -1898,6 +1916,7 @@ struct cmf_ensemble {
   std::vector<int64_t> read_step;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   ForkedRun forked;
+  FetchRing ring;
 };
 
 namespace {
@@ -2355,7 +2374,7 @@ int cmf_ensemble_get_populations(cmf_ensemble *E, int32_t index, double *f) {
   double *df = nullptr;
   if (hipMalloc((void **)&df, bytes) != hipSuccess) return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_get_state(rp.desc.q, E->storage, rp.cp, ens_replica_buffer(E, index), df, E->stream);
-  if (e == hipSuccess) e = fetch(f, df, bytes, E->stream);
+  if (e == hipSuccess) e = fetch(E->ring, f, df, bytes, E->stream);
   (void)hipFree(df);
   if (e != hipSuccess) return fail(CMF_EHIP, "ensemble get_populations failed: %s", hipGetErrorString(e));
   return CMF_OK;

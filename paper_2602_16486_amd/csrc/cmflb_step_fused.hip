@@ -18,7 +18,7 @@
 // per step with 1 / 3 / 5 / 7 / 9 steps per launch.  The sums of a step's
 // statistics run in the next step's time on the wave that has no sites (in the
 // sites' waves, ahead of their work, they took 0.8 us per step).  FP32 with
-// statistics: 64^2 5.96 -> 1.90, 200^2 6.36 -> 2.64, 400 x 300 8.50 -> 4.94 us
+// statistics: 64^2 5.96 -> 1.70, 200^2 6.36 -> 2.59, 400 x 300 8.50 -> 4.85 us
 // per step; the floor of 200^2 is 0.5 us (2.9 MB per step, or 342
 // instructions per site).
 #include "cmflb_step.h"
