@@ -243,7 +243,9 @@ int cmf_get_launch(cmf_lattice *lat, cmf_launch *out);
  * the site), only the speed and the summation order of the statistics.
  * From then on every step is one launch of that shape, also for the small
  * D2Q9 boxes that otherwise take several steps per launch, until
- * cmf_autotune.  Synchronises; drops captured graphs. */
+ * cmf_autotune.  Synchronises; drops captured graphs, and a lattice that had
+ * some (a run of 32 steps or more came first) takes direct steps from then
+ * on, here and in cmf_autotune: set the shape before the first run. */
 int cmf_set_launch(cmf_lattice *lat, int32_t block, int32_t grid);
 
 /* Autotuner: time every candidate launch shape (block 64..256, up to the
@@ -442,7 +444,8 @@ int cmf_ensemble_get_tiles(cmf_ensemble *ens, cmf_ensemble_tiles *out);
  * it (the noise is keyed by the site), only the speed and the summation
  * order of the statistics.  Synchronises; rebuilds the tile map (may
  * reallocate it and the partial sums: CMF_ENOMEM) and drops captured
- * graphs.  Errors: CMF_EINVAL, CMF_ENOMEM, CMF_EHIP. */
+ * graphs; an ensemble that had some takes direct steps from then on (as
+ * cmf_set_launch).  Errors: CMF_EINVAL, CMF_ENOMEM, CMF_EHIP. */
 int cmf_ensemble_set_tiles(cmf_ensemble *ens, int32_t spt9, int32_t spt3d);
 
 /* Autotuner of the tile shape (the batched-ensemble configuration of the

@@ -1,0 +1,52 @@
+"""The C ABI's host code (cmflb_capi.hip) against a runtime without a device
+(capi_host_driver.hip): what it allocates, captures and launches for calls
+whose effect a GPU test does not show.  CPU only; built with the address
+sanitizer where the toolchain has it."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2602_16486_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    try:
+        cxx = build.clangxx()
+    except RuntimeError as e:
+        pytest.skip(str(e))
+    tmp = tmp_path_factory.mktemp("capi_host")
+    exe = str(tmp / "driver")
+    flags = ["-x", "hip", "--offload-host-only", f"--offload-arch={build.ARCH}", "-O1", "-g",
+             "-std=c++17", "-Wno-unused-function", "-Wno-option-ignored"]
+    objs = []
+    # one cuid-less object may hold the fat binary's plain symbol names
+    for src, cuid in ((os.path.join(ROOT, "paper_2602_16486_amd", "csrc", "cmflb_capi.hip"), "none"),
+                      (os.path.join(ROOT, "tests", "capi_host_driver.hip"), "hash")):
+        objs.append(str(tmp / (os.path.basename(src) + ".o")))
+        subprocess.run([cxx, *flags, "-Xarch_host", "-fsanitize=address", f"-fuse-cuid={cuid}",
+                        "-c", src, "-o", objs[-1]], check=True)
+    subprocess.run([cxx, "-Xarch_host", "-fsanitize=address", *objs, "-o", exe, "-lpthread"], check=True)
+
+    def run(what):
+        r = subprocess.run([exe, what], capture_output=True, text=True, timeout=120,
+                           env=dict(os.environ, ASAN_OPTIONS="detect_leaks=1:exitcode=23"))
+        assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-4000:])
+        lines = r.stdout.split("\n")
+        # graph executables, streams, events, device and pinned bytes at the end
+        assert "left 0 0 0 0 0" in lines, r.stdout
+        return lines
+    return run
+
+
+def test_graphs_are_captured_at_most_once_per_parity(driver):
+    """A lattice or ensemble whose captured graphs were dropped by a new shape
+    takes direct steps from then on: at most one capture per buffer parity
+    in its life, every step taken, and graphs as before where the shape was
+    set before the first run."""
+    out = dict(line.split(" captures ") for line in driver("graphs") if " captures " in line)
+    assert int(out["lattice"]) <= 2 and int(out["ensemble"]) <= 2
+    assert out["tuned"] == "1 launches 10"
