@@ -606,6 +606,24 @@ int choose_tile_rows(const cmf_lattice *L) {
 
 int ntiles_for(const cmf_lattice *L, int block) { return tiles_for(L->desc, block); }
 
+// the runtime launches grids of fewer than 2^32 threads
+bool launchable(int64_t grid, int block) { return grid * block < (int64_t)1 << 32; }
+
+// One tile per workgroup, as long as the grid is launchable and the two slots
+// of partial sums that a lattice needs at least take kStatRingBytes or 1/64 of
+// the populations: tiles of full wavefronts stay far below that (1024^3 D3Q27
+// FP32: 0.8 GB beside 232), but a box of one or few sites per row has a tile
+// per row (1 x 4096 x 4096: 3.2 GB beside 7.2).  Workgroups beyond the limit
+// stride over the tiles instead.
+int one_tile_grid(const cmf_lattice *L, int block) {
+  const int64_t state = (int64_t)L->q * L->N * storage_bytes(L->storage) * (L->in_place ? 1 : 2);
+  const int64_t bytes = state / 64 > (int64_t)kStatRingBytes ? state / 64 : (int64_t)kStatRingBytes;
+  int64_t g = bytes / (2 * (int64_t)sizeof(double) * kPartStride);
+  if (!launchable(g, block)) g = (((int64_t)1 << 32) - 1) / block;
+  const int nt = ntiles_for(L, block);
+  return g < nt ? (int)g : nt;
+}
+
 // Workgroups of an untuned lattice.  FP32 and FP64 3-D steps wait for memory:
 // one tile per workgroup (D3Q27 FP32 / FP64 us per step against 2 per CU:
 // 50^3 14.5 / - against 20.3, 100^3 48.3 / 131 against 77.3 / 231, 128^3 82.3 / 214
@@ -619,7 +637,7 @@ int default_grid(const cmf_lattice *L, int block) {
   if (storage_bytes(L->storage) == 2) return 16 * L->cus;
   if (L->q == 9 && L->N < ((int64_t)1 << 22)) return 4 * L->cus * (256 / block);
   if (L->q == 9 && L->storage == kF64) return 16 * L->cus;
-  return ntiles_for(L, block);
+  return one_tile_grid(L, block);
 }
 
 // Destroy the captured runs of a lattice or ensemble whose launch shape
@@ -1561,7 +1579,7 @@ int cmf_autotune(cmf_lattice *L, int32_t steps_per_trial, cmf_launch *trials, in
     int last = -1;
     for (int g : grids) {
       const int gg = g < ntiles_for(L, b) ? g : ntiles_for(L, b);
-      if (gg == last) continue;
+      if (gg == last || !launchable(gg, b)) continue;
       last = gg;
       rc = apply_launch(L, b, gg, L->amp, L->scale);
       if (rc != CMF_OK) break;

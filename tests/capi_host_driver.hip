@@ -8,6 +8,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 #include <map>
 #include <vector>
@@ -26,6 +27,8 @@ struct Graph {
   int64_t by = 0;
 };
 
+constexpr size_t kDeviceBytes = (size_t)288 << 30;
+uint64_t threads = 0;  // most threads of one step launch
 int captures = 0, graph_launches = 0, execs = 0, direct_steps = 0, streams = 0, events = 0;
 bool capturing = false;
 Graph recorded;
@@ -74,8 +77,9 @@ hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
   return hipSuccess;
 }
 hipError_t hipMalloc(void **p, size_t n) {
-  *p = malloc(n);  // pages that nothing touches stay unbacked
-  if (!*p) return hipErrorOutOfMemory;
+  if (live + n > kDeviceBytes) return hipErrorOutOfMemory;
+  *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  if (*p == MAP_FAILED) return hipErrorOutOfMemory;
   sizes[*p] = n;
   live += n;
   most = live > most ? live : most;
@@ -83,8 +87,8 @@ hipError_t hipMalloc(void **p, size_t n) {
 }
 hipError_t hipFree(void *p) {
   live -= sizes.at(p);
+  munmap(p, sizes.at(p));
   sizes.erase(p);
-  free(p);
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
@@ -104,8 +108,8 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
   memcpy(d, s, n);
   return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
-  memcpy(d, s, n);
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, hipStream_t) {
+  if (kind != hipMemcpyDeviceToDevice) memcpy(d, s, n);
   return hipSuccess;
 }
 hipError_t hipMemset(void *, int, size_t) { return hipSuccess; }
@@ -181,7 +185,8 @@ hipError_t bump(int64_t *p, int64_t by) {
 }  // namespace
 
 hipError_t launch_step(int, int, bool, bool, int, const void *, const void *, void *, const int64_t *,
-                       int, double *, int, int, hipStream_t) {
+                       int, double *, int grid, int block, hipStream_t) {
+  threads = (uint64_t)grid * block > threads ? (uint64_t)grid * block : threads;
   direct_steps += !capturing;
   return hipSuccess;
 }
@@ -287,11 +292,43 @@ void graphs() {
   cmf_ensemble_destroy(E);
 }
 
+// boxes with many more tiles than lanes are full of: what an untuned lattice
+// and the tuner launch, and the device memory beside the populations
+void shapes() {
+  const int boxes[][4] = {{27, 1, 4096, 4096}, {27, 1, 8192, 8192}, {27, 3, 2048, 2048}, {19, 2, 4096, 2048},
+                          {19, 1, 1 << 24, 1}, {9, 1, 1 << 25, 1}, {9, 2, 1 << 22, 1}, {27, 70, 512, 512},
+                          {27, 256, 256, 256}, {27, 1024, 1024, 1024}, {9, 4096, 4096, 1}, {19, 50, 50, 50}};
+  for (auto &b : boxes)
+    for (int storage = 0; storage < 4; ++storage)
+      for (uint32_t flags : {0u, CMF_FLAG_IN_PLACE}) {
+        cmf_desc d = desc(b[0], b[1], b[2], b[3], storage);
+        d.flags = flags;
+        const size_t population = cmf_external_bytes(&d);
+        if (!population || population > kDeviceBytes) continue;
+        cmf_lattice *L = nullptr;
+        threads = most = 0;
+        CHECK(cmf_create(&d, nullptr, &L) == CMF_OK);
+        CHECK(cmf_step(L, 9) == CMF_OK);
+        cmf_launch s;
+        CHECK(cmf_get_launch(L, &s) == CMF_OK);
+        printf("box %d %d %d %d storage %d flags %u block %d grid %d threads %llu population %zu beside %zu",
+               b[0], b[1], b[2], b[3], storage, flags, s.block, s.grid, (unsigned long long)threads,
+               population, most - population);
+        threads = 0;
+        const int rc = cmf_autotune(L, 1, nullptr, 0, nullptr);
+        // (a copy of the state has to fit as well)
+        CHECK(rc == CMF_OK || (rc == CMF_ENOMEM && population + population / 2 > kDeviceBytes));
+        printf(" tuner %llu\n", (unsigned long long)threads);
+        cmf_destroy(L);
+      }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "graphs")) graphs();
+  if (!strcmp(what, "shapes")) shapes();
   printf("left %d %d %d %zu %zu\n", execs, streams, events, live, pinned);
   return 0;
 }

@@ -50,3 +50,19 @@ def test_graphs_are_captured_at_most_once_per_parity(driver):
     out = dict(line.split(" captures ") for line in driver("graphs") if " captures " in line)
     assert int(out["lattice"]) <= 2 and int(out["ensemble"]) <= 2
     assert out["tuned"] == "1 launches 10"
+
+
+def test_untuned_launches_and_their_partial_sums_are_bounded(driver):
+    """One tile per workgroup only while the grid is one that the runtime
+    launches (below 2^32 threads) and the partial sums take at most 256 MB or
+    1/64 of the populations: boxes of one or few sites per row have as many
+    tiles as rows.  The tuner launches no larger grid either."""
+    boxes = [line.split() for line in driver("shapes") if line.startswith("box ")]
+    assert len(boxes) > 80
+    for b in boxes:
+        v = dict(zip(b[5::2], map(int, b[6::2])))
+        assert 0 < v["threads"] < 2 ** 32 and v["tuner"] < 2 ** 32, b
+        # (and series, second-level rows and the step counter: under 2 MB)
+        assert v["beside"] <= max(256 << 20, v["population"] // 64) + (2 << 20), b
+    full = [b for b in boxes if b[1:5] == ["27", "1024", "1024", "1024"] and b[6] == "1" and b[8] == "0"]
+    assert full and all(b[12] == str(1024 ** 3 // 256) for b in full)  # one tile per workgroup
