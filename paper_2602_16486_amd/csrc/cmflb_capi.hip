@@ -18,7 +18,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -884,8 +883,9 @@ hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, FetchRing &rin
   threads.reserve(kFetchThreads);
   try {
     for (int t = 0; t < kFetchThreads; ++t) threads.emplace_back(work);
-  } catch (const std::system_error &) {
-    // fewer threads, or none: the copies below need at least one
+  } catch (...) {
+    // no thread or no memory for one: those that run are enough, if any do,
+    // and must not be left joinable by an exception
   }
   if (threads.empty()) return hipErrorOutOfMemory;
   hipError_t e = hipSuccess;

@@ -11,6 +11,7 @@
 #include <sys/mman.h>
 
 #include <map>
+#include <new>
 #include <vector>
 
 #include "../include/cmflb.h"
@@ -44,6 +45,17 @@ std::map<void *, size_t> sizes, pins;
   } while (0)
 
 }  // namespace
+
+// the allocation of this thread that fails (counted down; < 0: none)
+thread_local int fail_at = -1;
+
+void *operator new(size_t n) {
+  if (fail_at >= 0 && fail_at-- == 0) throw std::bad_alloc();
+  if (void *p = malloc(n)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 extern "C" {
 hipError_t hipStreamCreate(hipStream_t *s) {
@@ -80,7 +92,10 @@ hipError_t hipMalloc(void **p, size_t n) {
   if (live + n > kDeviceBytes) return hipErrorOutOfMemory;
   *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (*p == MAP_FAILED) return hipErrorOutOfMemory;
+  const int keep = fail_at;
+  fail_at = -1;  // only the library's allocations fail
   sizes[*p] = n;
+  fail_at = keep;
   live += n;
   most = live > most ? live : most;
   return hipSuccess;
@@ -93,7 +108,10 @@ hipError_t hipFree(void *p) {
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
   *p = malloc(n);
+  const int keep = fail_at;
+  fail_at = -1;
   pins[*p] = n;
+  fail_at = keep;
   pinned += n;
   most_pinned = pinned > most_pinned ? pinned : most_pinned;
   return hipSuccess;
@@ -323,12 +341,34 @@ void shapes() {
       }
 }
 
+// populations of 14 MB fetched while one allocation after another fails
+void allocations() {
+  const cmf_desc d = desc(27, 40, 40, 40, 1);
+  const int64_t n = 27 * 40 * 40 * 40;
+  cmf_lattice *L = nullptr;
+  CHECK(cmf_create(&d, nullptr, &L) == CMF_OK);
+  std::vector<double> f(n);
+  int failed = 0;
+  for (int k = 0; k < 24; ++k) {
+    for (auto &x : f) x = -1.0;
+    fail_at = k;
+    const int rc = cmf_get_populations(L, f.data());
+    failed += fail_at < 0;
+    fail_at = -1;
+    CHECK(rc == CMF_OK);
+    for (int64_t i = 0; i < n; ++i) CHECK(f[i] == (double)i);
+  }
+  printf("allocations failed %d\n", failed);
+  cmf_destroy(L);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "graphs")) graphs();
   if (!strcmp(what, "shapes")) shapes();
+  if (!strcmp(what, "allocations")) allocations();
   printf("left %d %d %d %zu %zu\n", execs, streams, events, live, pinned);
   return 0;
 }

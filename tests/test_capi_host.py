@@ -66,3 +66,10 @@ def test_untuned_launches_and_their_partial_sums_are_bounded(driver):
         assert v["beside"] <= max(256 << 20, v["population"] // 64) + (2 << 20), b
     full = [b for b in boxes if b[1:5] == ["27", "1024", "1024", "1024"] and b[6] == "1" and b[8] == "0"]
     assert full and all(b[12] == str(1024 ** 3 // 256) for b in full)  # one tile per workgroup
+
+
+def test_large_copies_survive_failing_allocations(driver):
+    """Whichever host allocation of a large copy fails, the copy is made (by
+    fewer threads or the runtime alone) and nothing is thrown."""
+    out = dict(line.split(" failed ") for line in driver("allocations") if " failed " in line)
+    assert int(out["allocations"]) >= 6  # the chunk flags, the thread list, four threads
