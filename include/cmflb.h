@@ -191,8 +191,9 @@ int cmf_set_populations(cmf_lattice *lat, const double *f);
  * of eq. lbe before its collision, Sec. 2.1) into q x N host doubles
  * (canonical layout).  Allocates a temporary device buffer of q N doubles.
  * Arrays of 8 MB and more (here and in the other calls that return fields)
- * pass through 24 MB of pinned host memory that the lattice or ensemble then
- * keeps until it is destroyed.
+ * pass through 24 MB of pinned host memory, shared by the lattices and
+ * ensembles of the process (up to four times as much while threads copy at
+ * the same time) and freed once those that used it are destroyed.
  * Synchronous.  Errors: CMF_EINVAL (NULL argument), CMF_ENOMEM, CMF_EHIP. */
 int cmf_get_populations(cmf_lattice *lat, double *f);
 

@@ -312,18 +312,15 @@ int capture_forked(hipStream_t s, ForkedRun &F, bool stats, int K, int64_t *step
   return CMF_OK;
 }
 
-// The pinned chunks of large copies to the host (see fetch) of one lattice or
-// ensemble, from its first such copy until its end.
+// The pinned chunks of large copies to the host (see fetch), of one device.
 constexpr size_t kFetchChunk = (size_t)4 << 20;
 constexpr int kFetchSlots = 6, kFetchThreads = 4;
 
 struct FetchRing {
   char *pin = nullptr;
+  int device = -1;
   hipEvent_t ready[kFetchSlots] = {};
-  FetchRing() = default;
-  FetchRing(const FetchRing &) = delete;
-  FetchRing &operator=(const FetchRing &) = delete;
-  ~FetchRing() { release(); }
+  bool busy = false;  // guarded by the pool's mutex, as is `device` while not busy
   void release() {
     for (auto &e : ready) {
       if (e) (void)hipEventDestroy(e);
@@ -331,17 +328,72 @@ struct FetchRing {
     }
     if (pin) (void)hipHostFree(pin);
     pin = nullptr;
+    device = -1;
   }
-  bool init() {
-    if (pin) return true;
+  bool init(int dev) {
+    if (pin && device == dev) return true;
+    release();
     bool ok = true;
     for (auto &e : ready) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipHostMalloc((void **)&pin, kFetchSlots * kFetchChunk, hipHostMallocDefault) == hipSuccess;
-    if (!ok) {
+    if (ok) {
+      device = dev;
+    } else {
       (void)hipGetLastError();
       release();
     }
     return ok;
+  }
+};
+
+// The rings of the process: one while copies come one after the other, up to
+// kFetchRings while threads copy at the same time (further ones leave the
+// copy to the runtime), freed once no lattice or ensemble that used them is
+// left.  Pinned for each call instead, a ring took 0.3 ms of it, and 4 ms once
+// three ensembles were asked in turn (54 MB 5.9 against 2.2 ms); kept by each
+// lattice, a hundred of them held 2.4 GB.
+constexpr int kFetchRings = 4;
+struct FetchPool {
+  std::mutex mu;
+  FetchRing ring[kFetchRings];
+  int users = 0;
+};
+FetchPool g_fetch;  // (frees nothing at exit, when the runtime may be gone)
+
+// A lattice's or ensemble's part in the pool, from its first large copy on.
+struct FetchUser {
+  bool joined = false;
+  FetchUser() = default;
+  FetchUser(const FetchUser &) = delete;
+  FetchUser &operator=(const FetchUser &) = delete;
+  ~FetchUser() {
+    if (!joined) return;
+    std::lock_guard<std::mutex> lk(g_fetch.mu);
+    if (--g_fetch.users == 0)
+      for (auto &r : g_fetch.ring) r.release();
+  }
+  // a ring of the current device for one copy, or NULL
+  FetchRing *take() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+    FetchRing *got = nullptr;
+    {
+      std::lock_guard<std::mutex> lk(g_fetch.mu);
+      if (!joined) ++g_fetch.users;
+      joined = true;
+      for (auto &r : g_fetch.ring)
+        if (!r.busy && (!got || (got->device != dev && r.device == dev))) got = &r;
+      if (got) got->busy = true;
+    }
+    if (got && !got->init(dev)) {
+      give(got);
+      got = nullptr;
+    }
+    return got;
+  }
+  void give(FetchRing *r) {
+    std::lock_guard<std::mutex> lk(g_fetch.mu);
+    r->busy = false;
   }
 };
 
@@ -388,7 +440,7 @@ struct cmf_lattice {
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   bool graphs_dropped = false;  // a new launch shape dropped captured graphs
   ForkedRun forked;
-  FetchRing ring;
+  FetchUser fetches;
   char *vel_ws = nullptr;  // velocity statistics: VelState, counts, block sums
   // structure factor
   int sk_nbins = 0;
@@ -848,9 +900,7 @@ int run_fused(cmf_lattice *L, int n) {
 // against 56 GB/s of the link to pinned memory.  Large arrays therefore go
 // through a ring of pinned chunks that kFetchThreads threads empty into the
 // caller's array, whose page faults they share (57 MB into a new numpy array 5.8 ->
-// 2.1 ms, 453 MB 45 -> 12).  The ring stays with the lattice: pinned for each
-// call it took 0.3 ms of it, and 4 ms once three ensembles were asked in turn
-// (54 MB 5.9 against 2.2 ms).
+// 2.1 ms, 453 MB 45 -> 12).
 
 // chunks 0 .. n - 1 in order: copies enqueued and waited for by this thread
 // (the only one that calls the runtime), emptied by the others; chunk c uses
@@ -920,17 +970,19 @@ hipError_t fetch_chunks(char *dst, const char *src, size_t bytes, FetchRing &rin
 
 // `bytes` from device memory at src to dst, after the work already on s;
 // returns when they are there (through the default stream, as hipMemcpy).
-hipError_t fetch(FetchRing &ring, void *dst, const void *src, size_t bytes, hipStream_t s) {
+hipError_t fetch(FetchUser &user, void *dst, const void *src, size_t bytes, hipStream_t s) {
   const hipError_t w = hipStreamSynchronize(s);
   if (w != hipSuccess) return w;
   if (bytes >= 2 * kFetchChunk) {
-    if (ring.init()) {
+    if (FetchRing *ring = user.take()) {
+      hipError_t e = hipErrorOutOfMemory;
       try {
-        const hipError_t e = fetch_chunks((char *)dst, (const char *)src, bytes, ring);
-        if (e == hipSuccess) return e;
-        (void)hipGetLastError();
+        e = fetch_chunks((char *)dst, (const char *)src, bytes, *ring);
       } catch (const std::bad_alloc &) {
       }
+      user.give(ring);
+      if (e == hipSuccess) return e;
+      (void)hipGetLastError();
     }
   }
   return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
@@ -1303,7 +1355,7 @@ int cmf_get_populations(cmf_lattice *L, double *f) {
   if (hipMalloc((void **)&df, bytes) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_get_state(L->q, L->storage, conv(L), L->buf[L->parity], df, L->stream);
-  if (e == hipSuccess) e = fetch(L->ring, f, df, bytes, L->stream);
+  if (e == hipSuccess) e = fetch(L->fetches, f, df, bytes, L->stream);
   (void)hipFree(df);
   if (e != hipSuccess) return fail(CMF_EHIP, "get_populations failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -1697,8 +1749,8 @@ int cmf_get_macro(cmf_lattice *L, double *rho, double *u) {
   if (hipMalloc((void **)&d, bytes) != hipSuccess)
     return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_macro(L->q, L->storage, conv(L), L->buf[L->parity], d, d + L->N, L->stream);
-  if (e == hipSuccess && rho) e = fetch(L->ring, rho, d, sizeof(double) * L->N, L->stream);
-  if (e == hipSuccess && u) e = fetch(L->ring, u, d + L->N, sizeof(double) * 3 * L->N, L->stream);
+  if (e == hipSuccess && rho) e = fetch(L->fetches, rho, d, sizeof(double) * L->N, L->stream);
+  if (e == hipSuccess && u) e = fetch(L->fetches, u, d + L->N, sizeof(double) * 3 * L->N, L->stream);
   (void)hipFree(d);
   if (e != hipSuccess) return fail(CMF_EHIP, "get_macro failed: %s", hipGetErrorString(e));
   return CMF_OK;
@@ -1944,7 +1996,7 @@ struct cmf_ensemble {
   hipGraphExec_t graph[2] = {nullptr, nullptr};
   bool graphs_dropped = false;  // a new tile shape dropped captured graphs
   ForkedRun forked;
-  FetchRing ring;
+  FetchUser fetches;
 };
 
 namespace {
@@ -2398,7 +2450,7 @@ int cmf_ensemble_get_populations(cmf_ensemble *E, int32_t index, double *f) {
   double *df = nullptr;
   if (hipMalloc((void **)&df, bytes) != hipSuccess) return fail(CMF_ENOMEM, "hipMalloc of %zu bytes failed", bytes);
   hipError_t e = launch_get_state(rp.desc.q, E->storage, rp.cp, ens_replica_buffer(E, index), df, E->stream);
-  if (e == hipSuccess) e = fetch(E->ring, f, df, bytes, E->stream);
+  if (e == hipSuccess) e = fetch(E->fetches, f, df, bytes, E->stream);
   (void)hipFree(df);
   if (e != hipSuccess) return fail(CMF_EHIP, "ensemble get_populations failed: %s", hipGetErrorString(e));
   return CMF_OK;

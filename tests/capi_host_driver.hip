@@ -11,7 +11,9 @@
 #include <sys/mman.h>
 
 #include <map>
+#include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "../include/cmflb.h"
@@ -35,6 +37,7 @@ bool capturing = false;
 Graph recorded;
 size_t live = 0, most = 0, pinned = 0, most_pinned = 0;
 std::map<void *, size_t> sizes, pins;
+std::mutex mu;  // guards what calls from several threads count
 
 #define CHECK(cond)                                                \
   do {                                                             \
@@ -72,12 +75,14 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+  std::lock_guard<std::mutex> lk(mu);
   ++events;
   *e = (hipEvent_t)malloc(1);
   return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) {
+  std::lock_guard<std::mutex> lk(mu);
   --events;
   free(e);
   return hipSuccess;
@@ -89,6 +94,7 @@ hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
   return hipSuccess;
 }
 hipError_t hipMalloc(void **p, size_t n) {
+  std::lock_guard<std::mutex> lk(mu);
   if (live + n > kDeviceBytes) return hipErrorOutOfMemory;
   *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (*p == MAP_FAILED) return hipErrorOutOfMemory;
@@ -101,12 +107,14 @@ hipError_t hipMalloc(void **p, size_t n) {
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+  std::lock_guard<std::mutex> lk(mu);
   live -= sizes.at(p);
   munmap(p, sizes.at(p));
   sizes.erase(p);
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+  std::lock_guard<std::mutex> lk(mu);
   *p = malloc(n);
   const int keep = fail_at;
   fail_at = -1;
@@ -117,6 +125,7 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
   return hipSuccess;
 }
 hipError_t hipHostFree(void *p) {
+  std::lock_guard<std::mutex> lk(mu);
   pinned -= pins.at(p);
   pins.erase(p);
   free(p);
@@ -362,6 +371,42 @@ void allocations() {
   cmf_destroy(L);
 }
 
+// many lattices and ensembles whose populations are fetched, in turn and by
+// several threads at once
+void pinned_memory() {
+  cmf_desc d = desc(27, 40, 40, 40, 1);
+  const int64_t n = 27 * 40 * 40 * 40;
+  std::vector<cmf_lattice *> lats(40);
+  auto fetch = [&](cmf_lattice *L) {
+    std::vector<double> f(n, -1.0);
+    CHECK(cmf_get_populations(L, f.data()) == CMF_OK);
+    for (int64_t i = 0; i < n; ++i) CHECK(f[i] == (double)i);
+  };
+  for (auto &L : lats) {
+    CHECK(cmf_create(&d, nullptr, &L) == CMF_OK);
+    fetch(L);
+  }
+  cmf_ensemble *E = nullptr;
+  CHECK(cmf_ensemble_create(&d, 1, nullptr, &E) == CMF_OK);
+  std::vector<double> f(n);
+  CHECK(cmf_ensemble_get_populations(E, 0, f.data()) == CMF_OK && f[n - 1] == (double)(n - 1));
+  printf("pinned in turn %zu\n", most_pinned);
+  std::vector<std::thread> threads;
+  for (int t = 0; t < 10; ++t)
+    threads.emplace_back([&, t] {
+      for (int r = 0; r < 3; ++r)
+        for (int k = t; k < 40; k += 10) fetch(lats[k]);
+    });
+  for (auto &t : threads) t.join();
+  printf("pinned at once %zu\n", most_pinned);
+  for (auto L : lats) cmf_destroy(L);
+  cmf_ensemble_destroy(E);
+  printf("pinned after %zu\n", pinned);
+  CHECK(cmf_create(&d, nullptr, &lats[0]) == CMF_OK);
+  fetch(lats[0]);
+  cmf_destroy(lats[0]);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -369,6 +414,7 @@ int main(int argc, char **argv) {
   if (!strcmp(what, "graphs")) graphs();
   if (!strcmp(what, "shapes")) shapes();
   if (!strcmp(what, "allocations")) allocations();
+  if (!strcmp(what, "pinned")) pinned_memory();
   printf("left %d %d %d %zu %zu\n", execs, streams, events, live, pinned);
   return 0;
 }

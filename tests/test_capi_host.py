@@ -73,3 +73,13 @@ def test_large_copies_survive_failing_allocations(driver):
     fewer threads or the runtime alone) and nothing is thrown."""
     out = dict(line.split(" failed ") for line in driver("allocations") if " failed " in line)
     assert int(out["allocations"]) >= 6  # the chunk flags, the thread list, four threads
+
+
+def test_pinned_memory_is_bounded_and_given_back(driver):
+    """Forty lattices and an ensemble share the pinned chunks of their large
+    copies: one set of 24 MB in turn, at most four sets in ten threads, none
+    once all of them are destroyed."""
+    out = dict(line[7:].rsplit(" ", 1) for line in driver("pinned") if line.startswith("pinned "))
+    assert int(out["in turn"]) == 24 << 20
+    assert int(out["at once"]) <= 4 * (24 << 20)
+    assert int(out["after"]) == 0
