@@ -350,6 +350,21 @@ void shapes() {
       }
 }
 
+// workgroup sizes of untuned lattices
+void blocks() {
+  const int boxes[][5] = {{9, 1030, 900, 1, 0}, {9, 1030, 900, 1, 1}, {9, 1290, 800, 1, 0}, {9, 600, 600, 1, 0},
+                          {27, 64, 64, 1, 1}, {27, 32, 32, 32, 1}, {19, 12, 14, 17, 2}, {27, 36, 36, 36, 1},
+                          {27, 50, 50, 50, 1}, {27, 256, 256, 256, 1}};
+  for (auto &b : boxes) {
+    const cmf_desc d = desc(b[0], b[1], b[2], b[3], b[4]);
+    cmf_lattice *L = nullptr;
+    cmf_launch s;
+    CHECK(cmf_create(&d, nullptr, &L) == CMF_OK && cmf_get_launch(L, &s) == CMF_OK);
+    printf("block %d %dx%dx%d %d %d\n", b[0], b[1], b[2], b[3], b[4], s.block);
+    cmf_destroy(L);
+  }
+}
+
 // populations of 14 MB fetched while one allocation after another fails
 void allocations() {
   const cmf_desc d = desc(27, 40, 40, 40, 1);
@@ -413,6 +428,7 @@ int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "graphs")) graphs();
   if (!strcmp(what, "shapes")) shapes();
+  if (!strcmp(what, "blocks")) blocks();
   if (!strcmp(what, "allocations")) allocations();
   if (!strcmp(what, "pinned")) pinned_memory();
   printf("left %d %d %d %zu %zu\n", execs, streams, events, live, pinned);

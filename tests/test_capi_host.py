@@ -83,3 +83,12 @@ def test_pinned_memory_is_bounded_and_given_back(driver):
     assert int(out["in turn"]) == 24 << 20
     assert int(out["at once"]) <= 4 * (24 << 20)
     assert int(out["after"]) == 0
+
+
+def test_workgroup_sizes_of_untuned_lattices(driver):
+    """3-D boxes of few tiles take 64 threads, measured faster than the fewest
+    lanes."""
+    got = {tuple(line.split()[1:4]): int(line.split()[4]) for line in driver("blocks") if line.startswith("block ")}
+    want = {("27", "64x64x1", "1"): 64, ("27", "32x32x32", "1"): 64, ("19", "12x14x17", "2"): 64,
+            ("27", "50x50x50", "1"): 256, ("27", "256x256x256", "1"): 256}
+    assert {k: got[k] for k in want} == want
