@@ -612,15 +612,19 @@ bool lookup_tuned(const cmf_lattice *L, int *block, int *grid) {
 // tile per workgroup, D3Q27 in tiles of a row, us per step at 64 / 128 / 192 / 256 threads: nx =
 // 300 FP32 110 / 101 / 104 / 114, FP64 207 / 218 / 222 / 262; nx = 200 FP32 160 /
 // 159 / 175 / 119, FP64 317 / 314 / 412 / 309; nx = 160 FP32 147 / 162 / 138; nx =
-// 100 FP32 58 / 48.  A 3-D box that 64-thread
+// 100 FP32 58 / 48.  D2Q9's cheaper sites leave more of a step to the
+// workgroups, so that fewer idle lanes weigh less (64 / 128 / 256 threads: 1030 x
+// 900 FP32 - / 19.4 / 17.2, FP64 without noise 25.2 / 24.9 / 23.6; 600 x 600 FP64
+// - / 15.3 / 17.0; 770 x 1000 FP32 - / 15.8 / 16.8).  A 3-D box that 64-thread
 // tiles cover with two per CU takes those: nothing queues, and a wave's latency
 // is the step (64 / 256 threads, D3Q27 FP32 and FP64: 16^3 7.2 / 7.8 and 10.8 / 12.7,
 // 32^3, 512 tiles, 7.4 / 7.8 and 11.8 / 13.4; 256 x 16 x 16, 1024 tiles, 9.4 / 8.8
 // and 14.6 / 14.4).
 int default_block(const cmf_desc &d, int cus) {
-  const bool f64 = d.storage == kF64;
-  if (d.q != 9 && tiles_for(d, 64) <= 2 * cus) return 64;
-  const double cost[4] = {f64 ? 1.1 : 1.35, f64 ? 1.05 : 1.1, 1.1, 1.0};
+  const bool f64 = d.storage == kF64, d2 = d.q == 9;
+  if (!d2 && tiles_for(d, 64) <= 2 * cus) return 64;
+  const double cost[4] = {!f64 ? 1.35 : d2 ? 1.18 : 1.1, d2 ? 1.13 : f64 ? 1.05 : 1.1,
+                          d2 ? 1.12 : 1.1, 1.0};
   int best = 0;
   double least = 0.0;
   for (int k = 0; k < 4; ++k) {

@@ -86,9 +86,12 @@ def test_pinned_memory_is_bounded_and_given_back(driver):
 
 
 def test_workgroup_sizes_of_untuned_lattices(driver):
-    """3-D boxes of few tiles take 64 threads, measured faster than the fewest
-    lanes."""
+    """Ragged D2Q9 boxes keep 256 threads unless a tenth and more of the lanes
+    would idle, and 3-D boxes of few tiles take 64: both measured faster than
+    the fewest lanes."""
     got = {tuple(line.split()[1:4]): int(line.split()[4]) for line in driver("blocks") if line.startswith("block ")}
-    want = {("27", "64x64x1", "1"): 64, ("27", "32x32x32", "1"): 64, ("19", "12x14x17", "2"): 64,
+    want = {("9", "1030x900x1", "0"): 256, ("9", "1030x900x1", "1"): 256, ("9", "600x600x1", "0"): 128,
+            ("27", "64x64x1", "1"): 64, ("27", "32x32x32", "1"): 64, ("19", "12x14x17", "2"): 64,
             ("27", "50x50x50", "1"): 256, ("27", "256x256x256", "1"): 256}
     assert {k: got[k] for k in want} == want
+    assert got["9", "1290x800x1", "0"] != 64
