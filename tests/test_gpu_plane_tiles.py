@@ -53,3 +53,24 @@ def test_plane_tiles_equal_an_ensemble(shape, q, storage):
                     lat.step(35)
                     assert np.array_equal(lat.get_populations(), ref), (rates, in_place, launch)
                     assert np.allclose(lat.stats(), ref_st, rtol=0, atol=atol), (rates, in_place, launch)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rates", ["paper", "isotropic"])
+def test_plane_tiles_of_a_box_that_draws_late(rates):
+    """D3Q27 FP32 beyond 2^22 sites draws its normals when it collides: plane
+    tiles there (rows of whole sectors, 200 x 200 x 112) against an ensemble,
+    bit for bit."""
+    q, shape = 27, (200, 200, 112)
+    n = W.n_sites(shape)
+    assert n > 1 << 22
+    kw = dict(tau=0.7, kT=1e-4, lam=rate_vector(q, 0.7, rates), seed=11, replica=0)
+    with Ensemble([dict(q=q, shape=shape, **kw)], storage="f32") as e:
+        e.step(5)
+        ref, ref_st = e.get_populations(0), e.stats(0)
+    with Lattice(q, shape, storage="f32", **kw) as lat:
+        # tiles of 256 sites of a plane, one per workgroup; a row would idle 56 lanes
+        assert lat.launch == (256, (200 * 200 + 255) // 256 * 112)
+        lat.step(5)
+        assert np.array_equal(lat.get_populations(), ref)
+        assert np.allclose(lat.stats(), ref_st, rtol=0, atol=1.1 * n * n * 2.0 ** -52)
