@@ -240,8 +240,9 @@ int cmf_get_launch(cmf_lattice *lat, cmf_launch *out);
 
 /* Set the launch shape: block in {64, 128, 192, 256}, grid >= 1 (capped at
  * the number of tiles: of `block` sites of a row, or, on 3-D boxes whose rows
- * would leave lanes idle, of `block` consecutive sites of a z plane).  Results do not depend on it (the noise is keyed by
- * the site), only the speed and the summation order of the statistics.
+ * would leave lanes idle, of `block` consecutive sites of a z plane).  Results
+ * do not depend on it (the noise is keyed by the site), only the speed and the
+ * summation order of the statistics.
  * From then on every step is one launch of that shape, also for the small
  * D2Q9 boxes that otherwise take several steps per launch, until
  * cmf_autotune.  Synchronises; drops captured graphs, and a lattice that had
@@ -250,9 +251,10 @@ int cmf_get_launch(cmf_lattice *lat, cmf_launch *out);
 int cmf_set_launch(cmf_lattice *lat, int32_t block, int32_t grid);
 
 /* Autotuner: time every candidate launch shape (block 64..256, up to the
- * row length where tiles are parts of a row; grid 1, 2, 4, 8, 16 and 32 x the compute-unit count, and one
- * tile per workgroup, which is the only grid of the small D2Q9 boxes that
- * take several steps per launch) with `steps_per_trial` real steps each (after one
+ * row length where tiles are parts of a row; grid 1, 2, 4, 8, 16 and 32 x the
+ * compute-unit count, and one tile per workgroup where the runtime launches
+ * that many, which is the only grid of the small D2Q9 boxes that take several
+ * steps per launch) with `steps_per_trial` real steps each (after one
  * untimed step; a step = fused kernel + statistics finalize), then restore the state, step counter and statistics ring
  * exactly as they were and keep the fastest shape.  The best shape is
  * remembered for the process under (device, q, storage, rates kind, box)
@@ -349,9 +351,8 @@ int cmf_get_macro(cmf_lattice *lat, double *rho, double *u);
  * fixed-order FP64 sums and integer counts.  The first call allocates a
  * workspace of about 300 KB that stays with the lattice; the velocities are
  * kept between the passes in the population buffer that the next step
- * overwrites, where the lattice owns two that hold them, and computed again
- * from the populations otherwise (in place, caller-owned buffers, 16-bit
- * storage where they do not fit).
+ * overwrites, where the lattice owns two, and computed again from the
+ * populations otherwise (in place, caller-owned buffers).
  * Errors: CMF_EINVAL (nbins outside [1, 4096] or xmax <= 0 with counts).
  * Synchronous. */
 int cmf_velocity_pdf(cmf_lattice *lat, int32_t nbins, double xmax, double *moments,

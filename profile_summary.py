@@ -319,7 +319,7 @@ def variants_summary(outdir):
             rb, wb = fk * COPY_BYTES / fc, wk * COPY_BYTES / wc
             lines.append(f"| {label} | {nf} | {rb / 1e9:.3f} | {wb / 1e9:.3f} | {(rb + wb) / alg:.3f} |")
     lines += ["", "The 16-bit kernels are bound by instruction issue (the Philox4x32-10 and Box-Muller noise is "
-              "about two thirds of it), not by HBM.  The in-place (AA) pair streams the same bytes in one buffer; "
+              "37-44 % of their instructions, k_step_valu_budget_256cube.md), not by HBM.  The in-place (AA) pair streams the same bytes in one buffer; "
               "bench.py's live figure for it is the average over even and odd steps.", ""]
     with open(os.path.join(ROOT, "profiles", "k_step_variants_256cube.md"), "w") as fh:
         fh.write("\n".join(lines))
