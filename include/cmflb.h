@@ -255,9 +255,9 @@ int cmf_set_launch(cmf_lattice *lat, int32_t block, int32_t grid);
  * compute-unit count, and one tile per workgroup where the runtime launches
  * that many, which is the only grid of the small D2Q9 boxes that take several
  * steps per launch) with `steps_per_trial` real steps each (after one
- * untimed step; a step = fused kernel + statistics finalize), then restore the state, step counter and statistics ring
- * exactly as they were and keep the fastest shape.  The best shape is
- * remembered for the process under (device, q, storage, rates kind, box)
+ * untimed step; a step = fused kernel + statistics finalize), then restore
+ * the state, step counter and statistics ring exactly as they were and keep
+ * the fastest shape.  The best shape is remembered for the process under (device, q, storage, rates kind, box)
  * and used by later cmf_create calls with the same key; when the environment
  * variable CMFLB_TUNE_CACHE names a file, entries are also read from and
  * appended to it.  Up to `cap` trials are written to `trials` (may be NULL);

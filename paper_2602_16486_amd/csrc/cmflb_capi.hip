@@ -481,20 +481,22 @@ void class_scales(int q, int storage, const float *scale, float *cs, float *ics)
   }
 }
 
-// Tiles per z plane of a 3-D lattice whose tiles are runs of the plane's
-// sites, 0 where they are parts of a row.  A step of a 3-D box issues for most
-// of its time, and lanes beyond the end of a row issue like any other: a row
-// of 50 takes a wave of 64, one of 150 three.  Runs of sites leave no lane
-// idle but those of a plane's last tile, for some 25 more address operations
-// per site (a lane's row is a vector value).  us per step, rows -> runs: D3Q27
-// FP32 50^3 14.3 -> 12.0, 32 x 96 x 96 20.7 -> 17.5, 100^3 44.3 -> 40.8, FP16 100^3 40.0 ->
-// 34.6, FP64 50^3 20.6 -> 19.1; D3Q19 BF16 72 x 60 x 50 15.6 -> 11.9, FP32 in place
-// 150 x 144 x 160 98.7 -> 87.9.  Where rows waste less than kFlatGain the gain is within
-// the noise or lost (D3Q27 FP32 120^3 76.3 -> 77.1, 250 x 120 x 90 110.6 -> 111.9).  D3Q27 in FP32 waits for
-// HBM once a box has outgrown the last-level cache, and a tile that ends
-// inside a 32-byte sector has its ends written in two parts: then only rows of
-// whole sectors go in runs (200 x 200 x 160 278 -> 268; 150 x 144 x 160, 22 % idle lanes, 145.4
-// -> 147.1; narrower rows of split sectors, which idle more, were not measured and stay rows).
+// Tiles per z plane of a 3-D lattice whose tiles are runs of the plane's sites,
+// 0 where they are parts of a row.  A step of a 3-D box issues for most of its
+// time, and lanes beyond the end of a row issue like any other: a row of 50
+// takes a wave of 64, one of 150 three.  Runs of sites leave no lane idle but
+// those of a plane's last tile, for some 25 more address operations per site (a
+// lane's row is a vector value).  us per step, rows -> runs: D3Q27 FP32 50^3
+// 14.3 -> 12.0, 32 x 96 x 96 20.7 -> 17.5, 100^3 44.3 -> 40.8, FP16 100^3 40.0
+// -> 34.6, FP64 50^3 20.6 -> 19.1; D3Q19 BF16 72 x 60 x 50 15.6 -> 11.9, FP32
+// in place 150 x 144 x 160 98.7 -> 87.9.  Where rows waste less than kFlatGain
+// the gain is within the noise or lost (D3Q27 FP32 120^3 76.3 -> 77.1, 250 x
+// 120 x 90 110.6 -> 111.9).  D3Q27 in FP32 waits for HBM once a box has
+// outgrown the last-level cache, and a tile that ends inside a 32-byte sector
+// has its ends written in two parts: then only rows of whole sectors go in runs
+// (200 x 200 x 160 278 -> 268; 150 x 144 x 160, 22 % idle lanes, 145.4 ->
+// 147.1; narrower rows of split sectors, which idle more, were not measured and
+// stay rows).
 constexpr double kFlatGain = 1.1;
 constexpr int64_t kFlatCached = (int64_t)1 << 21;  // sites
 int flat_plane_tiles(const cmf_desc &d, int block) {
@@ -641,21 +643,22 @@ int default_block(const cmf_desc &d, int cus) {
 
 // Small D2Q9 boxes take several steps per launch (cmflb_step_fused.hip): the
 // rows of a tile, 0 for a box that takes single steps.  The smallest tile with
-// at most one workgroup per CU, else two: within a step a CU's time is that of the sites around its tile as well, so that more
-// and smaller tiles cost less until they queue (FP32 us per step in tiles of
-// 4 / 8 / 12 / 16 rows: 100^2 2.03 / 2.22 / 2.32 / 2.52, 200^2 3.38 / 3.28 /
-// 2.64 / 2.78, 256^2 4.27 / 3.36 / 3.57 / 2.88; single steps 5.99, 6.36,
-// 6.43).  In FP64 two workgroups of 8 rows or more do not fit into a CU's LDS
-// (104 KB and more of 160) and run one after the other, which still saves time
-// (300^2 8.2 against 9.7; without noise 5.6 against 9.3).  Beyond two per CU the sites computed twice outweigh the launches
-// saved (400 x 300, 475 tiles of 16: 4.94 against 8.50; 700 x 500, 1408: 13.2
-// against 11.7; 512^2, 1024: FP32 9.2 against 10.3, FP16 9.5 against 8.1, FP64
-// 20.6 against 15.2; all before the first and last step of a launch had code
-// of their own, which takes 7-10 % off FP32 and 16-bit launches; the limit is
-// the same for every storage and was not measured again since).  A launch
-// shape that was asked for keeps single steps in that shape.  Boxes of this size keep their statistics in cell order
-// whether or not they can take several steps (in-place streaming and edges
-// up to kFusedSteps cannot).
+// at most one workgroup per CU, else two: within a step a CU's time is that of
+// the sites around its tile as well, so that more and smaller tiles cost less
+// until they queue (FP32 us per step in tiles of 4 / 8 / 12 / 16 rows: 100^2
+// 2.03 / 2.22 / 2.32 / 2.52, 200^2 3.38 / 3.28 / 2.64 / 2.78, 256^2 4.27 / 3.36
+// / 3.57 / 2.88; single steps 5.99, 6.36, 6.43).  In FP64 two workgroups of 8
+// rows or more do not fit into a CU's LDS (104 KB and more of 160) and run one
+// after the other, which still saves time (300^2 8.2 against 9.7 of single steps
+// in place).  Beyond two per CU the sites computed twice outweigh the launches saved (400 x 300, 475
+// tiles of 16: 4.94 against 8.50; 700 x 500, 1408: 13.2 against 11.7; 512^2,
+// 1024: FP32 9.2 against 10.3, FP16 9.5 against 8.1, FP64 20.6 against 15.2;
+// all before the first and last step of a launch had code of their own, which
+// takes 7-10 % off FP32 and 16-bit launches; the limit is the same for every
+// storage and was not measured again since).  A launch shape that was asked for
+// keeps single steps in that shape.  Boxes of this size keep their statistics
+// in cell order whether or not they can take several steps (in-place streaming
+// and edges up to kFusedSteps cannot).
 int choose_tile_rows(const cmf_lattice *L) {
   const cmf_desc &d = L->desc;
   if (L->q != 9 || L->shape_set) return 0;
